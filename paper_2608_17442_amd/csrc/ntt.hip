@@ -30,6 +30,7 @@
 // next to the data and generates those of bits 3..0 from one power per
 // thread (Context::d_tw3_*), so that no global load is waited on
 // between its butterflies.
+#include <algorithm>
 #include <type_traits>
 
 #include "butterfly.hpp"
@@ -432,7 +433,7 @@ struct RescaleMap {
   __device__ uint64_t* out(uint32_t g, uint32_t r) const { return w + ((size_t)g * last + r) * n; }
 };
 
-// ------------------------- basis conversion on the matrix cores (N = 2^16)
+// ------------------------------- basis conversion on the matrix cores
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
@@ -444,36 +445,42 @@ __device__ __forceinline__ uint64_t bal_bytes(double x) {
   return (uint64_t)(xi + 0x0080808080808080ll) ^ 0x0080808080808080ull;
 }
 
-// The conversion of k_bconv_outer for N = 2^16 and digits of at most 8
-// primes (a ninth source, for ModDown merged with the rescale, as one
-// Shoup product per value on the VALU), as an integer matrix product.  With x_a = sum_s x_a^s 256^s and
+// The conversion of k_bconv_outer for digits of at most 8 primes (a ninth
+// source, for ModDown merged with the rescale, as one Shoup product per value
+// on the VALU), as an integer matrix product.  With x_a = sum_s x_a^s 256^s and
 // c_(a,s) = 256^s hat_a mod m = sum_tau c^tau_(a,s) 256^tau (balanced
 // base-256 digits, LevelTables::mu_bytes),
 //     y = sum_a x_a hat_a = sum_tau 256^tau Q_tau  (mod m),
 //     Q_tau = sum_(a,s) x_a^s c^tau_(a,s),
-// an exact int32 (56 products of magnitude <= 2^14).  A wavefront owns the
-// 16 columns c0 .. c0 + 15 of the outer pass (values c0 + u + 4096 m) for
-// every target of its group.  Per quad of targets and index m, two
-// 16 x 16 x 64 int8 products (rows: 4 targets x tau 0..3, then tau 4..7;
-// columns: u; k: 8 sources x 8 digit bytes) give every Q, so that lane
-// (g, u) ends up with y of target g at c0 + u + 4096 m for all 16 m: the
-// column of the outer pass, which then runs in registers as in
-// k_bconv_outer.
-template <class Map, bool NINTH>
+// an exact int32 (56 products of magnitude <= 2^14).  A wavefront owns 16 C
+// columns of the outer pass, C = 16 / M (values c + 4096 m, c = c0 + u + 16 j,
+// j < C), i.e. 16 values per lane: value v = j M + m.  Per quad of targets and
+// value v, two 16 x 16 x 64 int8 products (rows: 4 targets x tau 0..3, then
+// tau 4..7; columns: u; k: 8 sources x 8 digit bytes) give every Q, so that
+// lane (g, u) ends up with y of target g at all its 16 values: whole columns
+// of the outer pass, which then runs in registers as in k_bconv_outer.
+// The quads of a column share one load of the digits; blockIdx.y deals them out
+// where one workgroup per column and group would leave the chip idle.
+template <int LOGM, class Map, bool NINTH>
 __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restrict__ pk,
                                            const double2* __restrict__ twf) {
-  constexpr uint32_t n = 1u << 16, LOGM = 4, M = 16;
+  constexpr uint32_t n = kBlock << LOGM;
+  constexpr int M = 1 << LOGM, C = 16 / M;
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t lg = lane >> 4, col = lane & 15;
   const uint32_t g = blockIdx.z;
-  const uint32_t c = (blockIdx.x * (kThreads / 64) + wave) * 16 + col;  // this lane's column
+  // this lane's first column
+  const uint32_t c = (blockIdx.x * (kThreads / 64) + wave) * (16 * C) + col;
+  // offset of value v = j M + m
+  auto at = [](int v) { return (uint32_t)(16 * (v / M)) + kBlock * (uint32_t)(v % M); };
   const uint32_t aj = map.aj(g), nt = map.targets(g);
+  if (4 * blockIdx.y >= nt) return;
   // a ninth digit source (ModDown merged with the rescale: q_{l-1} and eight
   // special primes) is added on the VALU
   const double* d8 = map.digits(g) + (size_t)8 * n + c;  // read only with NINTH (aj = 9)
-  // B operands: column col of product m holds value c + 4096 m of sources
-  // 2 lg (bytes 0..7) and 2 lg + 1 (bytes 8..15); a source past the digit
-  // reads a valid row and contributes zero
+  // B operands: column col of product v holds value v of sources 2 lg (bytes
+  // 0..7) and 2 lg + 1 (bytes 8..15); a source past the digit reads a valid
+  // row and contributes zero
   v4i b[16];
   {
     const double* dig = map.digits(g);
@@ -482,13 +489,13 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
     const double* r1 = dig + (size_t)min(a1, aj - 1) * n + c;
     const uint64_t k0 = a0 < aj ? ~0ull : 0ull, k1 = a1 < aj ? ~0ull : 0ull;
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const uint64_t p0 = bal_bytes(r0[kBlock * m]) & k0, p1 = bal_bytes(r1[kBlock * m]) & k1;
-      b[m] = v4i{(int)(uint32_t)p0, (int)(uint32_t)(p0 >> 32), (int)(uint32_t)p1,
+    for (int v = 0; v < 16; ++v) {
+      const uint64_t p0 = bal_bytes(r0[at(v)]) & k0, p1 = bal_bytes(r1[at(v)]) & k1;
+      b[v] = v4i{(int)(uint32_t)p0, (int)(uint32_t)(p0 >> 32), (int)(uint32_t)p1,
                  (int)(uint32_t)(p1 >> 32)};
     }
   }
-  for (uint32_t q0 = 0; q0 < nt; q0 += 4) {
+  for (uint32_t q0 = 4 * blockIdx.y; q0 < nt; q0 += 4 * gridDim.y) {
     // A operands: product row col = target q0 + col / 4, digit tau = col % 4
     // (first product) or 4 + col % 4 (second)
     const int8_t* tb = map.bytes(g, map.row(g, min(q0 + col / 4, nt - 1)));
@@ -506,9 +513,9 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
     const v4i zero = {0, 0, 0, 0};
     double x[16];
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const v4i dl = __builtin_amdgcn_mfma_i32_16x16x64_i8(alo, b[m], zero, 0, 0, 0);
-      const v4i dh = __builtin_amdgcn_mfma_i32_16x16x64_i8(ahi, b[m], zero, 0, 0, 0);
+    for (int v = 0; v < 16; ++v) {
+      const v4i dl = __builtin_amdgcn_mfma_i32_16x16x64_i8(alo, b[v], zero, 0, 0, 0);
+      const v4i dh = __builtin_amdgcn_mfma_i32_16x16x64_i8(ahi, b[v], zero, 0, 0, 0);
       // R = hi 2^32 + lo exactly (|lo| < 2^45, |hi| < 2^37), each |Q_tau| <=
       // 64 * 2^14 = 2^20, so digit pairs Q_t + 256 Q_t+1 still fit an int32
       // and are combined before the conversion to fp64; y = R - c q with
@@ -518,46 +525,55 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
       const double hi = __builtin_fma((double)dh[2], 65536.0, (double)(dh[0] + dh[1] * 256));
       const double cq = __builtin_rint(__builtin_fma(hi, k32, lo * qinv));
       double r = __builtin_fma(-cq, q, hi * 4294967296.0) + lo;
-      if constexpr (NINTH) r += mm_shoup(d8[kBlock * m], h8.x, h8.y, q);  // |r| < 1.2 q
-      x[m] = red_bal(r, q, qinv);
+      if constexpr (NINTH) r += mm_shoup(d8[at(v)], h8.x, h8.y, q);  // |r| < 1.2 q
+      x[v] = red_bal(r, q, qinv);
       // consume each pair of products here: otherwise the combination sinks
       // below the branch on tt and all 32 products (128 registers of
       // results) are held at once
-      asm volatile("" : "+v"(x[m]));
+      asm volatile("" : "+v"(x[v]));
     }
     if (tt >= nt) continue;
-    const double2* tw = twf + (size_t)prime * n;
+    if constexpr (LOGM == 0) {
+      uint64_t* out = map.out(g, trow);
 #pragma unroll
-    for (int s = 0; s < LOGM; ++s) {
-      const int H = M >> (s + 1);
+      for (int v = 0; v < 16; ++v) out[c + at(v)] = to_res(x[v], q, qinv);
+    } else {
+      const double2* tw = twf + (size_t)prime * n;
 #pragma unroll
-      for (int m = 0; m < M; ++m) {
-        if (m & H) continue;
-        const double2 w = tw[(1 << s) + (m >> (LOGM - s))];
-        const double u = (s % 2 == 0) ? red_bal(x[m], q, qinv) : x[m];
-        const double v = mm_shoup(x[m + H], w.x, w.y, q);
-        x[m] = u + v;
-        x[m + H] = u - v;
+      for (int s = 0; s < LOGM; ++s) {
+        const int H = M >> (s + 1);
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+          if (m & H) continue;
+          const double2 w = tw[(1 << s) + (m >> (LOGM - s))];
+#pragma unroll
+          for (int j = 0; j < C; ++j) {
+            const double u = (s % 2 == 0) ? red_bal(x[j * M + m], q, qinv) : x[j * M + m];
+            const double z = mm_shoup(x[j * M + m + H], w.x, w.y, q);
+            x[j * M + m] = u + z;
+            x[j * M + m + H] = u - z;
+          }
+        }
       }
-    }
-    double* outd = reinterpret_cast<double*>(map.out(g, map.row(g, tt)));
+      double* outd = reinterpret_cast<double*>(map.out(g, trow));
 #pragma unroll
-    for (int m = 0; m < 16; ++m) outd[c + kBlock * m] = x[m];
+      for (int v = 0; v < 16; ++v) outd[c + at(v)] = x[v];
+    }
   }
 }
 
 // Three waves per SIMD fit without spilling; the ninth-digit variant keeps
 // two (its extra loads would spill at three).
-template <class Map>
+template <int LOGM, class Map>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_bconv_mfma(
     Map map, const PrimeK* __restrict__ pk, const double2* __restrict__ twf) {
-  bconv_mfma<Map, false>(map, pk, twf);
+  bconv_mfma<LOGM, Map, false>(map, pk, twf);
 }
 
-template <class Map>
+template <int LOGM, class Map>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_bconv_mfma9(
     Map map, const PrimeK* __restrict__ pk, const double2* __restrict__ twf) {
-  bconv_mfma<Map, true>(map, pk, twf);
+  bconv_mfma<LOGM, Map, true>(map, pk, twf);
 }
 
 // ------------------------------------------------------------- inner pass
@@ -927,11 +943,9 @@ hipError_t launch_inverse(const Context* c, const RowSel& rs, uint32_t batch, ui
   return launch_inv_outer(c, rs, batch, limbs, st, s);
 }
 
-constexpr int kBconvTargets = 3;
-
-// The matrix-core conversion serves N = 2^16 for the maps that carry its
-// operand tables (ModUp, ModDown and ModDown merged with the rescale, with
-// digits of at most 8 primes plus at most one on the VALU).
+// The matrix-core conversion serves the maps that carry its operand tables
+// (ModUp, ModDown and ModDown merged with the rescale, with digits of at most
+// 8 primes plus at most one on the VALU).
 template <class Map>
 constexpr bool kMfmaMap = false;
 template <>
@@ -947,34 +961,64 @@ __host__ inline const int8_t* mfma_bytes(const ModdownRescaleMap& m) {
   return m.alpha <= 9 ? m.mr_bytes : nullptr;  // at most one digit past the eight
 }
 
-template <class Map>
-hipError_t launch_bconv_outer(const Context* c, const Map& map, uint32_t targets, uint32_t groups,
-                              hipStream_t s) {
-  constexpr int T = kBconvTargets;
+// Workgroups that fill the chip once at the matrix-core conversion's three
+// waves per SIMD (256 CUs).  A batch of one key switch has far fewer
+// (column block, digit) pairs, so its quads of targets go to different
+// workgroups; each of those loads the digits again, from L2: one rotation at
+// N = 2^16, 24 limbs, alpha = 8: 151 -> 138 us.
+constexpr uint32_t kBconvFill = 768;
+// Digits of fewer primes leave most of the product's 64-deep sums empty and
+// cost less as Shoup products on the VALU.  Rotations, matrix cores against
+// VALU (one / 30 at a time, us): alpha = 3, N = 2^15: 68 / 534 against
+// 66 / 518, N = 2^16: 90 / 1100 against 87 / 1055; alpha = 4, N = 2^14: 60 /
+// 360 against 64 / 365, N = 2^16: 98 / 1415 against 99 / 1405; alpha = 8,
+// N = 2^12: 49 / 199 against 59 / 235, N = 2^15: 95 / 1339 against 107 / 1452.
+constexpr uint32_t kMfmaMinDigit = 4;
+
+template <int LOGM, class Map>
+hipError_t launch_bconv_logm(const Context* c, const Map& map, uint32_t targets, uint32_t groups,
+                             hipStream_t s) {
+  constexpr uint32_t M = 1u << LOGM;
+  const double2* tw = c->d_tw_fwd;
   if constexpr (kMfmaMap<Map>) {
-    if (c->log_n == 16 && mfma_bytes(map)) {
-      const dim3 grid(kBlock / (16 * (kThreads / 64)), 1, groups);
+    if (mfma_bytes(map) && map.alpha >= kMfmaMinDigit) {
+      const uint32_t quads = (targets + 3) / 4, cols = 4 * M * groups;
+      const uint32_t split = std::min(quads, std::max(1u, kBconvFill / cols));
+      const dim3 grid(4 * M, split, groups);
       if constexpr (std::is_same_v<Map, ModdownRescaleMap>) {
         if (map.alpha > 8) {  // q_{l-1} and eight special primes
-          k_bconv_mfma9<Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, c->d_tw_fwd);
+          k_bconv_mfma9<LOGM, Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, tw);
           return hipGetLastError();
         }
       }
-      k_bconv_mfma<Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, c->d_tw_fwd);
+      k_bconv_mfma<LOGM, Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, tw);
       return hipGetLastError();
     }
   }
-  const dim3 grid(c->n / kBlock, (targets + T - 1) / T, groups), blk(kThreads);
-  const double2* tw = c->d_tw_fwd;
-  switch (c->log_n) {
-    case 12: k_bconv_outer<0, T, Map><<<grid, blk, 0, s>>>(map, c->log_n, c->d_pk, tw); break;
-    case 13: k_bconv_outer<1, T, Map><<<grid, blk, 0, s>>>(map, c->log_n, c->d_pk, tw); break;
-    case 14: k_bconv_outer<2, T, Map><<<grid, blk, 0, s>>>(map, c->log_n, c->d_pk, tw); break;
-    case 15: k_bconv_outer<3, T, Map><<<grid, blk, 0, s>>>(map, c->log_n, c->d_pk, tw); break;
-    case 16: k_bconv_outer<4, T, Map><<<grid, blk, 0, s>>>(map, c->log_n, c->d_pk, tw); break;
-    default: return hipErrorInvalidValue;
+  // VALU conversion: three targets share a load of the digits where that
+  // still fills the chip, else one target per workgroup (one rotation at
+  // N = 2^15, alpha = 3: 73 -> 66 us)
+  if (M * ((targets + 2) / 3) * groups >= kBconvFill) {
+    const dim3 grid(M, (targets + 2) / 3, groups);
+    k_bconv_outer<LOGM, 3, Map><<<grid, kThreads, 0, s>>>(map, c->log_n, c->d_pk, tw);
+  } else {
+    const dim3 grid(M, targets, groups);
+    k_bconv_outer<LOGM, 1, Map><<<grid, kThreads, 0, s>>>(map, c->log_n, c->d_pk, tw);
   }
   return hipGetLastError();
+}
+
+template <class Map>
+hipError_t launch_bconv_outer(const Context* c, const Map& map, uint32_t targets, uint32_t groups,
+                              hipStream_t s) {
+  switch (c->log_n) {
+    case 12: return launch_bconv_logm<0>(c, map, targets, groups, s);
+    case 13: return launch_bconv_logm<1>(c, map, targets, groups, s);
+    case 14: return launch_bconv_logm<2>(c, map, targets, groups, s);
+    case 15: return launch_bconv_logm<3>(c, map, targets, groups, s);
+    case 16: return launch_bconv_logm<4>(c, map, targets, groups, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace
