@@ -17,12 +17,12 @@ constexpr int kThreads = 256;
 
 // The 15 twiddles of one radix-16 step (1 + 2 + 4 + 8 groups), uniform.
 struct Tw15 {
-  double2 w[15];
+  double w[15];
 };
 template <int OFF>
 struct TwArg {
   const Tw15* t;
-  __device__ __forceinline__ double2 operator()(int gi) const { return t->w[OFF + gi]; }
+  __device__ __forceinline__ double operator()(int gi) const { return t->w[OFF + gi]; }
 };
 
 // One radix-16 step (four radix-2 stages, 32 butterflies per thread) per
@@ -37,14 +37,14 @@ __global__ __launch_bounds__(kThreads) void k_calib_bfly(Tw15 tw, double q, doub
   for (int r = 0; r < 16; ++r) x[r] = (double)((t * 16u + r) % 1000003u);
   for (uint32_t i = 0; i < iters; ++i) {
     if constexpr (INV) {
-      gs_st<1, true>(x, TwArg<7>{&tw}, q, qinv);
-      gs_st<2, false>(x, TwArg<3>{&tw}, q, qinv);
-      gs_st<4, true>(x, TwArg<1>{&tw}, q, qinv);
-      gs_st<8, false>(x, TwArg<0>{&tw}, q, qinv);
+      gs_st<1, kGs1.m[0]>(x, TwArg<7>{&tw}, q, qinv);
+      gs_st<2, kGs1.m[1]>(x, TwArg<3>{&tw}, q, qinv);
+      gs_st<4, kGs1.m[2]>(x, TwArg<1>{&tw}, q, qinv);
+      gs_st<8, kGs1.m[3]>(x, TwArg<0>{&tw}, q, qinv);
     } else {
       ct_st<8, true>(x, TwArg<0>{&tw}, q, qinv);
       ct_st<4, false>(x, TwArg<1>{&tw}, q, qinv);
-      ct_st<2, true>(x, TwArg<3>{&tw}, q, qinv);
+      ct_st<2, false>(x, TwArg<3>{&tw}, q, qinv);
       ct_st<1, false>(x, TwArg<7>{&tw}, q, qinv);
     }
   }
@@ -226,8 +226,7 @@ int calib_valu(Context* c, int kind, uint32_t iters, double* rate, hipStream_t s
   const double q = (double)c->primes[0], qinv = 1.0 / q;
   Tw15 tw;
   for (int i = 0; i < 15; ++i) {
-    const double w = std::floor(q / (3.0 + i));
-    tw.w[i] = double2{w, w / q};
+    tw.w[i] = std::floor(q / (3.0 + i));
   }
   hipEvent_t e0, e1;
   if (int rc = hip_check(hipEventCreate(&e0), "hipEventCreate")) return rc;

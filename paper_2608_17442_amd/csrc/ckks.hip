@@ -105,8 +105,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_acc(ConvTable tab, const uint
 // -tw[brv(e - N)] otherwise (tw = forward twiddle table).
 // Evaluation of X^m at the point of index k (prime i): the value psi^e,
 // e = (2 brv(k) + 1) m mod 2N, as a table twiddle and a sign (psi^N = -1).
-__device__ __forceinline__ double2 monomial_w(uint32_t k, uint32_t m, uint32_t log_n, uint32_t i,
-                                              const double2* __restrict__ twf, bool* neg) {
+__device__ __forceinline__ double monomial_w(uint32_t k, uint32_t m, uint32_t log_n, uint32_t i,
+                                              const double* __restrict__ twf, bool* neg) {
   const uint32_t n = 1u << log_n;
   const uint32_t b = __builtin_bitreverse32(k) >> (32 - log_n);
   const uint32_t e = ((2u * b + 1u) * m) & (2u * n - 1u);
@@ -118,25 +118,25 @@ __device__ __forceinline__ double2 monomial_w(uint32_t k, uint32_t m, uint32_t l
 __global__ __launch_bounds__(kThreads) void k_monomial(const uint64_t* in, uint64_t* out,
                                                        uint32_t log_n, uint32_t m,
                                                        const PrimeK* __restrict__ pk,
-                                                       const double2* __restrict__ twf) {
+                                                       const double* __restrict__ twf) {
   const uint32_t n = 1u << log_n;
   const uint32_t r = blockIdx.y, i = r >> 1;
   const uint32_t k = blockIdx.x * kThreads + threadIdx.x;
   if (k >= n) return;
   const PrimeK P = pk[i];
   bool neg;
-  const double2 w = monomial_w(k, m, log_n, i, twf, &neg);
+  const double w = monomial_w(k, m, log_n, i, twf, &neg);
   const size_t o = (size_t)r * n + k;
-  double v = mm_shoup(ld(in + o), w.x, w.y, P.q);
+  double v = mm_var(ld(in + o), w, P.q, P.qinv);
   st(out + o, neg ? -v : v, P.q, P.qinv);
 }
 
 // Pair blockIdx.z of the table, row blockIdx.y (limb r / 2, component r % 2).
 // X^(N/2) and X^(3N/2) evaluate to -+ psi^(N/2) at every point, so the
-// monomial is one Shoup product and a sign.
+// monomial is one product and a sign.
 __global__ __launch_bounds__(kThreads) void k_pair(PairTable tab, bool split, uint32_t log_n,
                                                    const PrimeK* __restrict__ pk,
-                                                   const double2* __restrict__ twf) {
+                                                   const double* __restrict__ twf) {
   const uint32_t n = 1u << log_n;
   const uint32_t r = blockIdx.y, i = r >> 1, j = blockIdx.z;
   const uint32_t k = blockIdx.x * kThreads + threadIdx.x;
@@ -145,13 +145,13 @@ __global__ __launch_bounds__(kThreads) void k_pair(PairTable tab, bool split, ui
   const size_t o = (size_t)r * n + k;
   bool neg;
   if (!split) {
-    const double2 w = monomial_w(k, n / 2, log_n, i, twf, &neg);
-    const double v = mm_shoup(ld(tab.y[j] + o), w.x, w.y, P.q);
+    const double w = monomial_w(k, n / 2, log_n, i, twf, &neg);
+    const double v = mm_var(ld(tab.y[j] + o), w, P.q, P.qinv);
     st(tab.x[j] + o, ld(tab.x[j] + o) + (neg ? -v : v), P.q, P.qinv);
   } else {
     const double a = ld(tab.x[j] + o), b = ld(tab.y[j] + o);
-    const double2 w = monomial_w(k, 3 * n / 2, log_n, i, twf, &neg);
-    const double v = mm_shoup(a - b, w.x, w.y, P.q);
+    const double w = monomial_w(k, 3 * n / 2, log_n, i, twf, &neg);
+    const double v = mm_var(a - b, w, P.q, P.qinv);
     st(tab.first[j] + o, a + b, P.q, P.qinv);
     st(tab.second[j] + o, neg ? -v : v, P.q, P.qinv);
   }

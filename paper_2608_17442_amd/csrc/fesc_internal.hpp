@@ -30,7 +30,7 @@ namespace fesc {
 struct PrimeK {        // per-prime constants read by kernels
   double q;            // the prime
   double qinv;         // fl(1/q)
-  double ninv, ninvp;  // N^-1 mod q and fl(N^-1 / q)
+  double ninv, ninvp;  // N^-1 mod q, balanced, and fl(N^-1 / q)
   uint64_t qu;         // the prime as an integer
   uint64_t pad[3];
 };
@@ -93,6 +93,18 @@ __device__ __forceinline__ uint64_t to_res(double x, double q, double qinv) {
   return (uint64_t)__double_as_longlong(v) & 0x000FFFFFFFFFFFFFull;
 }
 
+// The same for |x| < 2 q, q < 2^50, with three operations less: the shift of
+// the quotient by 1/2 - 2^-51 makes its rounding the floor of x / q.  (x / q is
+// a multiple of 1 / q > 2^-50, so the shifted quotient stays at least 2^-51 from
+// every half-integer; its error, |x / q| 2^-53 and one rounding below 2^-52, is
+// smaller.)
+constexpr double kFloorShift = -0.5 + 1.0 / 2251799813685248.0;
+__device__ __forceinline__ uint64_t to_res_2q(double x, double q, double qinv) {
+  const double c = __builtin_rint(__builtin_fma(x, qinv, kFloorShift));
+  const double v = __builtin_fma(-c, q, x) + kTwo52;
+  return (uint64_t)__double_as_longlong(v) & 0x000FFFFFFFFFFFFFull;
+}
+
 // ------------------------------------------------------------- host side
 
 #define FESC_MAX_PRIMES 64
@@ -110,13 +122,13 @@ struct LevelTables {
   double2* md_pinv = nullptr;  // [level]                   P^-1 mod q_i
   double2* pmod = nullptr;     // [L]                       P mod q_i
   double2* rs_inv = nullptr;   // [level]                   q_{level-1}^-1 mod q_i
-  double2* mu_inv_n = nullptr; // [level]  N^-1 (Q_D/q_i)^-1 mod q_i (q_i in digit D)
-  double2* md_inv_n = nullptr; // [alpha]  N^-1 (P/p_k)^-1 mod p_k
-  double2* rs_ninv = nullptr;  // [1]      N^-1 mod q_{level-1}
+  double2* mu_inv_n = nullptr; // [level]  N^-1 (Q_D/q_i)^-1 mod q_i (q_i in digit D), balanced
+  double2* md_inv_n = nullptr; // [alpha]  N^-1 (P/p_k)^-1 mod p_k, balanced
+  double2* rs_ninv = nullptr;  // [1]      N^-1 mod q_{level-1}, balanced
   double2* one = nullptr;      // [level]  1 (with 1/q_i)
   // ModDown merged with the rescale (division by M = P q_{level-1}); digit
   // sources m_0 = q_{level-1}, m_{1+k} = p_k
-  double2* mr_inv_n = nullptr; // [alpha+1]  N^-1 (M/m_j)^-1 mod m_j (m_0: N^-1, the row holding x P^-1)
+  double2* mr_inv_n = nullptr; // [alpha+1]  N^-1 (M/m_j)^-1 mod m_j, balanced (m_0: N^-1, the row holding x P^-1)
   double2* mr_hat = nullptr;   // [level-1][alpha+1]  (M/m_j) mod q_i
   // int8 operands of the matrix-core basis conversion (k_bconv_mfma, alpha
   // <= 8): per target row 512 bytes [tau 8][lane group 4][16]; byte b of
@@ -134,10 +146,10 @@ struct Context {
   std::vector<uint64_t> primes;   // ext order: q_0..q_{L-1}, p_0..p_{alpha-1}
   std::vector<uint64_t> psi;      // smallest primitive 2N-th root per prime
   PrimeK* d_pk = nullptr;         // [L+alpha]
-  // [L+alpha][N] {w, w/q}, w = psi^brv(i) (inverse: psi^-brv(i)) as the
-  // balanced representative in [-q/2, q/2]
-  double2* d_tw_fwd = nullptr;
-  double2* d_tw_inv = nullptr;
+  // [L+alpha][N] psi^brv(i) (inverse: psi^-brv(i)) as the balanced
+  // representative in [-q/2, q/2]
+  double* d_tw_fwd = nullptr;
+  double* d_tw_inv = nullptr;
   // the powers used by the radix-16 step on index bits 3..0 of the 4096-point
   // inner NTT blocks, re-ordered [L+alpha][N/4096][15][256] (see ntt.hip)
   double* d_tw3_fwd = nullptr;

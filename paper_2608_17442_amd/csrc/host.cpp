@@ -187,7 +187,7 @@ void* scratch_get(Context* c, size_t bytes, int* err) {
 static int build_tables(Context* c) {
   const uint32_t n = c->n, np = (uint32_t)c->ext_count();
   std::vector<PrimeK> pk(np);
-  std::vector<double2> fwd((size_t)np * n), inv((size_t)np * n);
+  std::vector<double> fwd((size_t)np * n), inv((size_t)np * n);
   const uint32_t nblk = n / 4096;
   std::vector<double> fwd3((size_t)np * nblk * 256), inv3(fwd3.size());
   std::vector<uint64_t> pw(n);
@@ -195,18 +195,18 @@ static int build_tables(Context* c) {
     const uint64_t q = c->primes[i];
     const double qd = (double)q;
     const uint64_t ninv = h_inv(n % q, q);
-    pk[i] = PrimeK{qd, 1.0 / qd, (double)ninv, (double)ninv / qd, q, {0, 0, 0}};
+    const double ninvd = ninv > q / 2 ? -(double)(q - ninv) : (double)ninv;
+    pk[i] = PrimeK{qd, 1.0 / qd, ninvd, ninvd / qd, q, {0, 0, 0}};
     for (int dir = 0; dir < 2; ++dir) {
       const uint64_t root = dir == 0 ? c->psi[i] : h_inv(c->psi[i], q);
       pw[0] = 1;
       for (uint32_t e = 1; e < n; ++e) pw[e] = h_mulmod(pw[e - 1], root, q);
-      double2* t = (dir == 0 ? fwd.data() : inv.data()) + (size_t)i * n;
+      double* t = (dir == 0 ? fwd.data() : inv.data()) + (size_t)i * n;
       // balanced representative, |w| <= q/2 (halves the error term of the
-      // Shoup products, which the lazy butterflies rely on)
+      // products, which the lazy butterflies rely on)
       for (uint32_t k = 0; k < n; ++k) {
         const uint64_t e = pw[bitrev(k, c->log_n)];
-        const double w = e > q / 2 ? -(double)(q - e) : (double)e;
-        t[k] = double2{w, w / qd};
+        t[k] = e > q / 2 ? -(double)(q - e) : (double)e;
       }
       // Block blk, thread e: psi_rev[(N + 4096 blk) / 2 + 8 e], the power from
       // which an inner pass generates the twiddles of index bits 3..0 of its
@@ -214,7 +214,7 @@ static int build_tables(Context* c) {
       double* t3 = (dir == 0 ? fwd3.data() : inv3.data()) + (size_t)i * nblk * 256;
       for (uint32_t blk = 0; blk < nblk; ++blk)
         for (uint32_t e = 0; e < 256; ++e)
-          t3[(size_t)blk * 256 + e] = t[((n + 4096 * blk) >> 1) + 8 * e].x;
+          t3[(size_t)blk * 256 + e] = t[((n + 4096 * blk) >> 1) + 8 * e];
     }
   }
   // device encoding tables
@@ -253,16 +253,16 @@ static int build_tables(Context* c) {
                                 hipMemcpyHostToDevice), "hipMemcpy")))
     return rc == FESC_ERR_HIP ? fail(FESC_ERR_OOM, "encoding table allocation failed") : rc;
   if ((rc = hip_check(hipMalloc(&c->d_pk, sizeof(PrimeK) * np), "hipMalloc")) ||
-      (rc = hip_check(hipMalloc(&c->d_tw_fwd, sizeof(double2) * fwd.size()), "hipMalloc")) ||
-      (rc = hip_check(hipMalloc(&c->d_tw_inv, sizeof(double2) * inv.size()), "hipMalloc")) ||
+      (rc = hip_check(hipMalloc(&c->d_tw_fwd, sizeof(double) * fwd.size()), "hipMalloc")) ||
+      (rc = hip_check(hipMalloc(&c->d_tw_inv, sizeof(double) * inv.size()), "hipMalloc")) ||
       (rc = hip_check(hipMalloc(&c->d_tw3_fwd, sizeof(double) * fwd3.size()), "hipMalloc")) ||
       (rc = hip_check(hipMalloc(&c->d_tw3_inv, sizeof(double) * inv3.size()), "hipMalloc")))
     return rc == FESC_ERR_HIP ? fail(FESC_ERR_OOM, "table allocation failed") : rc;
   if ((rc = hip_check(hipMemcpy(c->d_pk, pk.data(), sizeof(PrimeK) * np, hipMemcpyHostToDevice),
                       "hipMemcpy")) ||
-      (rc = hip_check(hipMemcpy(c->d_tw_fwd, fwd.data(), sizeof(double2) * fwd.size(),
+      (rc = hip_check(hipMemcpy(c->d_tw_fwd, fwd.data(), sizeof(double) * fwd.size(),
                                 hipMemcpyHostToDevice), "hipMemcpy")) ||
-      (rc = hip_check(hipMemcpy(c->d_tw_inv, inv.data(), sizeof(double2) * inv.size(),
+      (rc = hip_check(hipMemcpy(c->d_tw_inv, inv.data(), sizeof(double) * inv.size(),
                                 hipMemcpyHostToDevice), "hipMemcpy")) ||
       (rc = hip_check(hipMemcpy(c->d_tw3_fwd, fwd3.data(), sizeof(double) * fwd3.size(),
                                 hipMemcpyHostToDevice), "hipMemcpy")) ||

@@ -26,10 +26,10 @@
 // transform.
 //
 // Twiddles: the outer passes read the bit-reversed power table (uniform per
-// stage); an inner pass stages its block's 255 twiddles of bits 11..4 in LDS
-// next to the data and generates those of bits 3..0 from one power per
-// thread (Context::d_tw3_*), so that no global load is waited on
-// between its butterflies.
+// stage); an inner pass reads its block's 15 twiddles of bits 11..8 through the
+// scalar cache, stages those of bits 7..4 in LDS next to the data and generates
+// those of bits 3..0 from one power per thread (Context::d_tw3_*), so that no
+// vector load is waited on between its butterflies.
 #include <algorithm>
 #include <type_traits>
 
@@ -60,47 +60,78 @@ __device__ __forceinline__ uint32_t lds_mid(uint32_t a, uint32_t b, uint32_t r) 
 __device__ __forceinline__ uint32_t lds_col(uint32_t t, uint32_t r) { return 17 * t + r; }
 constexpr int kLds = kBlock + kBlock / 16;
 
-// Inner passes: the twiddles of bits 11..4 staged in LDS per block.  For
-// index bits 11..8 (register distance H, distance 256 H) the group twiddle is
-// psi_rev[(N + B) / 512H + gi]; for bits 7..4 (distance 16 H) with a = bits
-// 11..8 of the thread's values it is psi_rev[(N + B) / 32H + a * 8/H + gi]
-// (B the block offset in the row): eight contiguous runs of the table, 255
-// values.  Entry t < 255 of the staging array lies in segment k = floor(log2(t + 1))
-// (the 2^k group twiddles of one stage) at index t + 1 - 2^k, i.e.
-// psi_rev[(N + B) / 2^(12 - k) + t + 1 - 2^k]; entries 255..261 are
-// psi_rev[1..7].  For bits 11..8 (distance 256 H) the stage of H uses
-// segment log2(8/H); for bits 7..4 (distance 16 H) segment 4 + log2(8/H), at
-// a * 8/H + gi.
-constexpr int kTwL = 262;
-__device__ __forceinline__ double2 block_twiddle(const double2* tw, uint32_t nb, uint32_t t) {
-  const uint32_t k = 31 - __builtin_clz(t + 1);  // t < 255
-  return tw[(nb >> (12 - k)) + t + 1 - (1u << k)];
+// Inner passes, twiddles.  For index bits 11..8 (register distance H, distance
+// 256 H) the group twiddle is psi_rev[(N + B) / 512H + gi] (B the block offset in
+// the row): the same for the whole workgroup, so it comes through the scalar
+// cache into scalar registers (TwU).  For bits 7..4 (distance 16 H) with a =
+// bits 11..8 of the thread's values it is psi_rev[(N + B) / 32H + a * 8/H + gi].
+// A wavefront holds the values of four a's, so it stages its own 60 of them in
+// LDS (TwL) and no barrier of the workgroup stands before their use: entry
+// 2^k + a 2^(k-4) + gi - 1 (k = 4 + log2(8/H)) is psi_rev[(N + B) / 2^(12 - k) +
+// a 2^(k-4) + gi].
+constexpr int kTwL = 255;
+struct StagedTwiddle {
+  double w;
+  uint32_t at;
+};
+__device__ __forceinline__ StagedTwiddle load_staged(const double* tw, uint32_t nb) {
+  const uint32_t wave = threadIdx.x >> 6, lane = min(threadIdx.x & 63, 59u);
+  const uint32_t k = 4 + (31 - __builtin_clz(lane / 4 + 1));  // 4, 8, 16, 32 lanes
+  const uint32_t i = lane + 4 - (1u << (k - 2)) + (wave << (k - 2));
+  return {tw[(nb >> (12 - k)) + i], (1u << k) - 1 + i};
 }
 struct TwL {
-  const double2* lt;
+  const double* lt;
   uint32_t off;
-  __device__ __forceinline__ double2 operator()(int gi) const { return lt[off + gi]; }
+  __device__ __forceinline__ double operator()(int gi) const { return lt[off + gi]; }
 };
+// Uniform twiddles in scalar registers: the 15 of bits 11..8 (entry 2^k - 1 +
+// gi: psi_rev[(N + B) / 2^(12 - k) + gi], k = log2(8/H)) and psi_rev[1..7].
+struct UniTw {
+  double top[15], c[7];
+  __device__ __forceinline__ UniTw(const double* tw, uint32_t nb) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int i = 0; i < (1 << k); ++i) top[(1 << k) - 1 + i] = tw[(nb >> (12 - k)) + i];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) c[i] = tw[i + 1];
+  }
+  // waits for them here, where the block's values are still on their way,
+  // instead of between the butterflies
+  __device__ __forceinline__ void settle() {
+#pragma unroll
+    for (int i = 0; i < 15; ++i) asm volatile("" : "+s"(top[i]));
+#pragma unroll
+    for (int i = 0; i < 7; ++i) asm volatile("" : "+s"(c[i]));
+  }
+};
+struct TwU {
+  const double* w;
+  __device__ __forceinline__ double operator()(int gi) const { return w[gi]; }
+};
+
+// Orders a wavefront's LDS accesses where its lanes exchange values among
+// themselves (the hardware performs them in program order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // Bits 3..0, generated instead of loaded: thread t's 16 consecutive values
 // are positions 16 j + r with j = (N + B) / 16 + t; brv(j) has its three low
 // bits clear, so psi_rev[j 8/H + gi] = psi_rev[j 8/H] psi_rev[gi] and
-// psi_rev[j 8/H] = b^(8/H) with b = psi_rev[8 j].  Each twiddle is formed as
-// the balanced representative (the table's value) and w' = w / q as w qinv
-// (as for the loaded ones).
+// psi_rev[j 8/H] = b^(8/H) with b = psi_rev[8 j].  The products are used as they
+// come, within kTwGen q.
 struct TwGen {
-  double base;         // psi_rev[j 8/H], balanced
-  const double2* c;    // psi_rev[1..7] (LDS)
+  double base;      // psi_rev[j 8/H]
+  const double* c;  // psi_rev[1..7] (uniform)
   double q, qinv;
-  __device__ __forceinline__ double2 operator()(int gi) const {
-    const double w =
-        gi == 0 ? base : red_bal(mm_shoup(base, c[gi - 1].x, c[gi - 1].y, q), q, qinv);
-    return double2{w, w * qinv};
+  __device__ __forceinline__ double operator()(int gi) const {
+    return gi == 0 ? base : mm_var(base, c[gi - 1], q, qinv);
   }
 };
-__device__ __forceinline__ double sq_bal(double b, double q, double qinv) {
-  return red_bal(mm_shoup(b, b, b * qinv, q), q, qinv);
-}
 
 }  // namespace
 
@@ -132,17 +163,17 @@ namespace {
 // M = 2^LOGM point columns at stride 4096; a thread holds C = 16/M columns,
 // c0 + 256 j (j < C), value m of column j in x[j*M + m].  Grid x = M.
 // Stage s (distance 4096 * M/2^(s+1)) uses psi_rev[2^s + m / 2^(LOGM-s)].
-// Forward stages reduce lazily as in ct_st (even s reduce).
+// Forward stages from canonical residues reduce nothing (below kCtOuter q).
 template <int LOGM>
 __global__ __launch_bounds__(kThreads) void k_fwd_outer(RowSel rs, uint32_t log_n,
                                                         const PrimeK* __restrict__ pk,
-                                                        const double2* __restrict__ twf) {
+                                                        const double* __restrict__ twf) {
   constexpr int M = 1 << LOGM, C = 16 / M;
   if (rs.skip()) return;
   const uint32_t n = 1u << log_n;
   const uint32_t prime = rs.prime();
   const double q = pk[prime].q, qinv = pk[prime].qinv;
-  const double2* tw = twf + (size_t)prime * n;
+  const double* tw = twf + (size_t)prime * n;
   uint64_t* row = rs.row();
   const uint32_t c0 = blockIdx.x * (kThreads * C) + threadIdx.x;
   double x[16];
@@ -156,11 +187,10 @@ __global__ __launch_bounds__(kThreads) void k_fwd_outer(RowSel rs, uint32_t log_
 #pragma unroll
     for (int m = 0; m < M; ++m) {
       if (m & H) continue;
-      const double2 w = tw[(1 << s) + (m >> (LOGM - s))];
+      const double w = tw[(1 << s) + (m >> (LOGM - s))];
 #pragma unroll
       for (int j = 0; j < C; ++j) {
-        const double u = (s % 2 == 0) ? red_bal(x[j * M + m], q, qinv) : x[j * M + m];
-        const double v = mm_shoup(x[j * M + m + H], w.x, w.y, q);
+        const double u = x[j * M + m], v = mm_var(x[j * M + m + H], w, q, qinv);
         x[j * M + m] = u + v;
         x[j * M + m + H] = u - v;
       }
@@ -177,36 +207,37 @@ __global__ __launch_bounds__(kThreads) void k_fwd_outer(RowSel rs, uint32_t log_
 struct InvCanon {
   __device__ __forceinline__ void operator()(uint64_t* row, uint32_t k, double x,
                                              const PrimeK& P) const {
-    row[k] = to_res(mm_shoup(x, P.ninv, P.ninvp, P.q), P.q, P.qinv);
+    row[k] = to_res_2q(mm_shoup(x, P.ninv, P.ninvp, P.q), P.q, P.qinv);
   }
 };
 
 // Final store of an inverse transform that feeds a fast basis conversion: the
 // centred digit [N^-1 f_i x]_q in (-q/2, q/2), stored as fp64 in place of the
-// residue.  f holds {N^-1 f_i mod q_i, /q_i} per limb i (blockIdx.z), where
-// f_i is the conversion's (Q_D/q_i)^-1.
+// residue.  f holds {N^-1 f_i mod q_i (balanced), /q_i} per limb i (blockIdx.z),
+// where f_i is the conversion's (Q_D/q_i)^-1.  The product lies within 1.2 q
+// (|x| < 5 q), near enough for red_bal's quotient to be the nearest integer:
+// x / q is at least 1 / 2q > 2^-51 away from a half, its error below 2^-51.
 struct InvDigit {
   const double2* f;
   __device__ __forceinline__ void operator()(uint64_t* row, uint32_t k, double x,
                                              const PrimeK& P) const {
     const double2 c = f[blockIdx.z];
-    reinterpret_cast<double*>(row)[k] =
-        center(red_full(mm_shoup(x, c.x, c.y, P.q), P.q, P.qinv), P.q);
+    reinterpret_cast<double*>(row)[k] = red_bal(mm_shoup(x, c.x, c.y, P.q), P.q, P.qinv);
   }
 };
 
-// Inverse: stages in reverse order (every other one reducing, as in gs_st),
-// then the final store (N^-1 scaling included).
+// Inverse: stages in reverse order (sums reduced as kGsOut says), then the final
+// store (N^-1 scaling included).
 template <int LOGM, class St>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_inv_outer(RowSel rs, uint32_t log_n,
                                                         const PrimeK* __restrict__ pk,
-                                                        const double2* __restrict__ twi, St st) {
+                                                        const double* __restrict__ twi, St st) {
   constexpr int M = 1 << LOGM, C = 16 / M;
   if (rs.skip()) return;
   const uint32_t n = 1u << log_n;
   const uint32_t prime = rs.prime();
   const PrimeK P = pk[prime];
-  const double2* tw = twi + (size_t)prime * n;
+  const double* tw = twi + (size_t)prime * n;
   uint64_t* row = rs.row();
   const double* rowd = reinterpret_cast<const double*>(row);
   const uint32_t c0 = blockIdx.x * (kThreads * C) + threadIdx.x;
@@ -221,12 +252,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
 #pragma unroll
     for (int m = 0; m < M; ++m) {
       if (m & H) continue;
-      const double2 w = tw[(1 << s) + (m >> (LOGM - s))];
+      const double w = tw[(1 << s) + (m >> (LOGM - s))];
 #pragma unroll
       for (int j = 0; j < C; ++j) {
         const double u = x[j * M + m], v = x[j * M + m + H];
-        x[j * M + m] = ((LOGM - 1 - s) % 2 == 0) ? red_bal(u + v, P.q, P.qinv) : u + v;
-        x[j * M + m + H] = mm_shoup(u - v, w.x, w.y, P.q);
+        // the plan's registers have M = 16 columns' stride: register m here
+        x[j * M + m] =
+            (kGsOut.m[LOGM - 1 - s] >> m) & 1u ? red_bal(u + v, P.q, P.qinv) : u + v;
+        x[j * M + m + H] = mm_var(u - v, w, P.q, P.qinv);
       }
     }
   }
@@ -252,7 +285,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
 template <int LOGM, int T, class Map>
 __global__ __launch_bounds__(kThreads) void k_bconv_outer(Map map, uint32_t log_n,
                                                           const PrimeK* __restrict__ pk,
-                                                          const double2* __restrict__ twf) {
+                                                          const double* __restrict__ twf) {
   constexpr int M = 1 << LOGM, C = 16 / M;
   const uint32_t g = blockIdx.z, t0 = blockIdx.y * T;
   const uint32_t nt = map.targets(g);
@@ -311,7 +344,7 @@ __global__ __launch_bounds__(kThreads) void k_bconv_outer(Map map, uint32_t log_
 #pragma unroll
       for (int v = 0; v < 16; ++v) out[c0 + kThreads * v] = to_res(x[v], q, qinv);
     } else {
-      const double2* tw = twf + (size_t)prime[i] * n;
+      const double* tw = twf + (size_t)prime[i] * n;
 #pragma unroll
       for (int v = 0; v < 16; ++v) x[v] = red_bal(x[v], q, qinv);
 #pragma unroll
@@ -320,11 +353,10 @@ __global__ __launch_bounds__(kThreads) void k_bconv_outer(Map map, uint32_t log_
 #pragma unroll
         for (int m = 0; m < M; ++m) {
           if (m & H) continue;
-          const double2 w = tw[(1 << s) + (m >> (LOGM - s))];
+          const double w = tw[(1 << s) + (m >> (LOGM - s))];
 #pragma unroll
           for (int j = 0; j < C; ++j) {
-            const double u = (s % 2 == 0) ? red_bal(x[j * M + m], q, qinv) : x[j * M + m];
-            const double v = mm_shoup(x[j * M + m + H], w.x, w.y, q);
+            const double u = x[j * M + m], v = mm_var(x[j * M + m + H], w, q, qinv);
             x[j * M + m] = u + v;
             x[j * M + m + H] = u - v;
           }
@@ -463,7 +495,7 @@ __device__ __forceinline__ uint64_t bal_bytes(double x) {
 // where one workgroup per column and group would leave the chip idle.
 template <int LOGM, class Map, bool NINTH>
 __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restrict__ pk,
-                                           const double2* __restrict__ twf) {
+                                           const double* __restrict__ twf) {
   constexpr uint32_t n = kBlock << LOGM;
   constexpr int M = 1 << LOGM, C = 16 / M;
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -525,8 +557,9 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
       const double hi = __builtin_fma((double)dh[2], 65536.0, (double)(dh[0] + dh[1] * 256));
       const double cq = __builtin_rint(__builtin_fma(hi, k32, lo * qinv));
       double r = __builtin_fma(-cq, q, hi * 4294967296.0) + lo;
-      if constexpr (NINTH) r += mm_shoup(d8[at(v)], h8.x, h8.y, q);  // |r| < 1.2 q
-      x[v] = red_bal(r, q, qinv);
+      if constexpr (NINTH)  // |r| < 1.2 q before the reduction, 0.5 q without it
+        r = red_bal(r + mm_shoup(d8[at(v)], h8.x, h8.y, q), q, qinv);
+      x[v] = r;
       // consume each pair of products here: otherwise the combination sinks
       // below the branch on tt and all 32 products (128 registers of
       // results) are held at once
@@ -536,20 +569,19 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
     if constexpr (LOGM == 0) {
       uint64_t* out = map.out(g, trow);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) out[c + at(v)] = to_res(x[v], q, qinv);
+      for (int v = 0; v < 16; ++v) out[c + at(v)] = to_res_2q(x[v], q, qinv);
     } else {
-      const double2* tw = twf + (size_t)prime * n;
+      const double* tw = twf + (size_t)prime * n;
 #pragma unroll
       for (int s = 0; s < LOGM; ++s) {
         const int H = M >> (s + 1);
 #pragma unroll
         for (int m = 0; m < M; ++m) {
           if (m & H) continue;
-          const double2 w = tw[(1 << s) + (m >> (LOGM - s))];
+          const double w = tw[(1 << s) + (m >> (LOGM - s))];
 #pragma unroll
           for (int j = 0; j < C; ++j) {
-            const double u = (s % 2 == 0) ? red_bal(x[j * M + m], q, qinv) : x[j * M + m];
-            const double z = mm_shoup(x[j * M + m + H], w.x, w.y, q);
+            const double u = x[j * M + m], z = mm_var(x[j * M + m + H], w, q, qinv);
             x[j * M + m] = u + z;
             x[j * M + m + H] = u - z;
           }
@@ -566,13 +598,13 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
 // two (its extra loads would spill at three).
 template <int LOGM, class Map>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_bconv_mfma(
-    Map map, const PrimeK* __restrict__ pk, const double2* __restrict__ twf) {
+    Map map, const PrimeK* __restrict__ pk, const double* __restrict__ twf) {
   bconv_mfma<LOGM, Map, false>(map, pk, twf);
 }
 
 template <int LOGM, class Map>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_bconv_mfma9(
-    Map map, const PrimeK* __restrict__ pk, const double2* __restrict__ twf) {
+    Map map, const PrimeK* __restrict__ pk, const double* __restrict__ twf) {
   bconv_mfma<LOGM, Map, true>(map, pk, twf);
 }
 
@@ -597,37 +629,40 @@ __device__ __forceinline__ void fwd_load(const uint64_t* row, uint32_t B, double
   }
 }
 
-// The 12 stages on values already loaded by fwd_load; lt: the block's
-// staged twiddles (visible to every thread), b: psi_rev[(N + B) / 2 + 8 t].
-__device__ __forceinline__ void fwd_transform(const double2* lt, double b, double q, double qinv,
-                                              double* lds, double (&x)[16]) {
+// The 12 stages on values already loaded by fwd_load; u: the uniform twiddles,
+// lt: the staged ones (written before the first barrier), b:
+// psi_rev[(N + B) / 2 + 8 t].
+__device__ __forceinline__ void fwd_transform(const UniTw& u, const double* lt, double b,
+                                              double q, double qinv, double* lds,
+                                              double (&x)[16]) {
   const uint32_t t = threadIdx.x, a = t >> 4, bb = t & 15;
   // bits 11..8
-  ct_st<8, true>(x, TwL{lt, 0}, q, qinv);
-  ct_st<4, false>(x, TwL{lt, 1}, q, qinv);
-  ct_st<2, true>(x, TwL{lt, 3}, q, qinv);
-  ct_st<1, false>(x, TwL{lt, 7}, q, qinv);
+  ct_st<8, kCtRed[0]>(x, TwU{u.top}, q, qinv);
+  ct_st<4, kCtRed[1]>(x, TwU{u.top + 1}, q, qinv);
+  ct_st<2, kCtRed[2]>(x, TwU{u.top + 3}, q, qinv);
+  ct_st<1, kCtRed[3]>(x, TwU{u.top + 7}, q, qinv);
 #pragma unroll
   for (int r = 0; r < 16; ++r) lds[lds_row(t, r)] = x[r];
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < 16; ++r) x[r] = lds[lds_mid(a, bb, r)];
   // bits 7..4
-  ct_st<8, true>(x, TwL{lt, 15 + a}, q, qinv);
-  ct_st<4, false>(x, TwL{lt, 31 + 2 * a}, q, qinv);
-  ct_st<2, true>(x, TwL{lt, 63 + 4 * a}, q, qinv);
-  ct_st<1, false>(x, TwL{lt, 127 + 8 * a}, q, qinv);
+  ct_st<8, kCtRed[4]>(x, TwL{lt, 15 + a}, q, qinv);
+  ct_st<4, kCtRed[5]>(x, TwL{lt, 31 + 2 * a}, q, qinv);
+  ct_st<2, kCtRed[6]>(x, TwL{lt, 63 + 4 * a}, q, qinv);
+  ct_st<1, kCtRed[7]>(x, TwL{lt, 127 + 8 * a}, q, qinv);
+  // the 16 threads of one a exchange their 256 values: one wavefront
 #pragma unroll
   for (int r = 0; r < 16; ++r) lds[lds_mid(a, bb, r)] = x[r];
-  __syncthreads();
+  wave_sync();
 #pragma unroll
   for (int r = 0; r < 16; ++r) x[r] = lds[lds_col(t, r)];
   // bits 3..0
-  const double b2 = sq_bal(b, q, qinv), b4 = sq_bal(b2, q, qinv);
-  ct_st<8, true>(x, TwGen{sq_bal(b4, q, qinv), lt + 255, q, qinv}, q, qinv);
-  ct_st<4, false>(x, TwGen{b4, lt + 255, q, qinv}, q, qinv);
-  ct_st<2, true>(x, TwGen{b2, lt + 255, q, qinv}, q, qinv);
-  ct_st<1, false>(x, TwGen{b, lt + 255, q, qinv}, q, qinv);
+  const double b2 = mm_var(b, b, q, qinv), b4 = mm_var(b2, b2, q, qinv);
+  ct_st<8, kCtRed[8]>(x, TwGen{mm_var(b4, b4, q, qinv), u.c, q, qinv}, q, qinv);
+  ct_st<4, kCtRed[9]>(x, TwGen{b4, u.c, q, qinv}, q, qinv);
+  ct_st<2, kCtRed[10]>(x, TwGen{b2, u.c, q, qinv}, q, qinv);
+  ct_st<1, kCtRed[11]>(x, TwGen{b, u.c, q, qinv}, q, qinv);
 }
 
 // An epilogue with nothing to load ahead of the transform.
@@ -637,20 +672,21 @@ struct NoPre {};
 // 11..8 in registers), moves to a*256 + 16 r + b (a = t/16, b = t%16; bits
 // 7..4) and to 16 t + r (bits 3..0); fwd_transform ends there.  Each transpose
 // writes exactly the LDS words the thread read in the previous one, so only
-// the reads need a barrier.  The kernel hands values t + 256 r to the
-// epilogue.
+// the reads need ordering: a barrier of the workgroup for the first and the
+// last, the middle one stays inside a wavefront.  The kernel hands values
+// t + 256 r to the epilogue.
 //
 // SINGLE: N = 4096, the pass reads uint64 residues; otherwise it reads the
 // outer pass's fp64 intermediate.  No global load is waited on inside the
-// transform: the block's twiddles of bits 11..4 are staged in LDS with the
-// data loads, those of bits 3..0 generated from one loaded power.
+// transform: its twiddles of bits 11..4 are loaded with the data, those of
+// bits 3..0 generated from one loaded power.
 template <bool SINGLE, class Epi>
 __global__ __launch_bounds__(kThreads) void k_fwd_inner(RowSel rs, uint32_t log_n,
                                                         const PrimeK* __restrict__ pk,
-                                                        const double2* __restrict__ twf,
+                                                        const double* __restrict__ twf,
                                                         const double* __restrict__ tw3, Epi epi) {
   __shared__ double lds[kLds];
-  __shared__ double2 lt[kTwL];
+  __shared__ double lt[kTwL];
   if (rs.skip()) return;
   const uint32_t n = 1u << log_n;
   const uint32_t prime = rs.prime();
@@ -658,9 +694,9 @@ __global__ __launch_bounds__(kThreads) void k_fwd_inner(RowSel rs, uint32_t log_
   uint64_t* row = rs.row();
   const uint32_t t = threadIdx.x;
   const uint32_t B = blockIdx.x * kBlock;
-  const double2* tw = twf + (size_t)prime * n;
-  if (t < 255) lt[t] = block_twiddle(tw, n + B, t);
-  if (t < 7) lt[255 + t] = tw[t + 1];
+  const double* tw = twf + (size_t)prime * n;
+  UniTw u(tw, n + B);
+  const StagedTwiddle st = load_staged(tw, n + B);
   // psi_rev[(N + B) / 2 + 8 t]
   const double b = tw3[((size_t)prime * (n / kBlock) + blockIdx.x) * kThreads + t];
   // operands of the epilogue loaded before the transform, so that their
@@ -668,8 +704,9 @@ __global__ __launch_bounds__(kThreads) void k_fwd_inner(RowSel rs, uint32_t log_
   const typename Epi::Pre pv = epi.pre(B + t, n);
   double x[16];
   fwd_load<SINGLE>(row, B, x);
-  __syncthreads();
-  fwd_transform(lt, b, q, qinv, lds, x);
+  u.settle();
+  lt[st.at] = st.w;
+  fwd_transform(u, lt, b, q, qinv, lds, x);
 #pragma unroll
   for (int r = 0; r < 16; ++r) lds[lds_col(t, r)] = x[r];
   __syncthreads();
@@ -685,7 +722,7 @@ struct StoreResidues {
   __device__ __forceinline__ void operator()(uint64_t* row, uint32_t k0, const double (&x)[16],
                                              double q, double qinv, uint32_t, Pre) const {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) row[k0 + 256 * r] = to_res(x[r], q, qinv);
+    for (int r = 0; r < 16; ++r) row[k0 + 256 * r] = to_res_2q(x[r], q, qinv);
   }
 };
 
@@ -727,60 +764,61 @@ struct LoadSources {
   }
 };
 
-// Inverse 4096-point blocks: the mirror image of k_fwd_inner (twiddles of
-// bits 11..4 staged in LDS, those of bits 3..0 generated).  Reads uint64
+// Inverse 4096-point blocks: the mirror image of k_fwd_inner, with one barrier
+// of the workgroup, before the last transpose.  Reads uint64
 // residues (16 consecutive values per thread), writes fp64 for the outer pass
 // or, if SINGLE, applies the final store St.
 template <bool SINGLE, class Ld, class St>
 __global__ __launch_bounds__(kThreads) void k_inv_inner(RowSel rs, uint32_t log_n,
                                                         const PrimeK* __restrict__ pk,
-                                                        const double2* __restrict__ twi,
+                                                        const double* __restrict__ twi,
                                                         const double* __restrict__ tw3, Ld ld,
                                                         St st) {
   __shared__ double lds[kLds];
-  __shared__ double2 lt[kTwL];
+  __shared__ double lt[kTwL];
   if (rs.skip()) return;
   const uint32_t n = 1u << log_n;
   const uint32_t prime = rs.prime();
   const PrimeK P = pk[prime];
   const double q = P.q, qinv = P.qinv;
-  const double2* tw = twi + (size_t)prime * n;
+  const double* tw = twi + (size_t)prime * n;
   uint64_t* row = rs.row();
   const uint32_t t = threadIdx.x, a = t >> 4, b = t & 15;
   const uint32_t B = blockIdx.x * kBlock;
-  if (t < 255) lt[t] = block_twiddle(tw, n + B, t);
-  if (t < 7) lt[255 + t] = tw[t + 1];
+  UniTw u(tw, n + B);
+  const StagedTwiddle sw = load_staged(tw, n + B);
   // psi_rev[(N + B) / 2 + 8 t] (inverse powers)
   const double b1 = tw3[((size_t)prime * (n / kBlock) + blockIdx.x) * kThreads + t];
   double x[16];
   ld(row, B + 16 * t, x, q, qinv);
-  __syncthreads();
+  u.settle();
+  lt[sw.at] = sw.w;
   // bits 3..0
-  const double b2 = sq_bal(b1, q, qinv), b4 = sq_bal(b2, q, qinv);
-  gs_st<1, true>(x, TwGen{b1, lt + 255, q, qinv}, q, qinv);
-  gs_st<2, false>(x, TwGen{b2, lt + 255, q, qinv}, q, qinv);
-  gs_st<4, true>(x, TwGen{b4, lt + 255, q, qinv}, q, qinv);
-  gs_st<8, false>(x, TwGen{sq_bal(b4, q, qinv), lt + 255, q, qinv}, q, qinv);
+  const double b2 = mm_var(b1, b1, q, qinv), b4 = mm_var(b2, b2, q, qinv);
+  gs_st<1, kGs0.m[0]>(x, TwGen{b1, u.c, q, qinv}, q, qinv);
+  gs_st<2, kGs0.m[1]>(x, TwGen{b2, u.c, q, qinv}, q, qinv);
+  gs_st<4, kGs0.m[2]>(x, TwGen{b4, u.c, q, qinv}, q, qinv);
+  gs_st<8, kGs0.m[3]>(x, TwGen{mm_var(b4, b4, q, qinv), u.c, q, qinv}, q, qinv);
 #pragma unroll
   for (int r = 0; r < 16; ++r) lds[lds_col(t, r)] = x[r];
-  __syncthreads();
+  wave_sync();
 #pragma unroll
   for (int r = 0; r < 16; ++r) x[r] = lds[lds_mid(a, b, r)];
   // bits 7..4
-  gs_st<1, true>(x, TwL{lt, 127 + 8 * a}, q, qinv);
-  gs_st<2, false>(x, TwL{lt, 63 + 4 * a}, q, qinv);
-  gs_st<4, true>(x, TwL{lt, 31 + 2 * a}, q, qinv);
-  gs_st<8, false>(x, TwL{lt, 15 + a}, q, qinv);
+  gs_st<1, kGs1.m[0]>(x, TwL{lt, 127 + 8 * a}, q, qinv);
+  gs_st<2, kGs1.m[1]>(x, TwL{lt, 63 + 4 * a}, q, qinv);
+  gs_st<4, kGs1.m[2]>(x, TwL{lt, 31 + 2 * a}, q, qinv);
+  gs_st<8, kGs1.m[3]>(x, TwL{lt, 15 + a}, q, qinv);
 #pragma unroll
   for (int r = 0; r < 16; ++r) lds[lds_mid(a, b, r)] = x[r];
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < 16; ++r) x[r] = lds[lds_row(t, r)];
   // bits 11..8
-  gs_st<1, true>(x, TwL{lt, 7}, q, qinv);
-  gs_st<2, false>(x, TwL{lt, 3}, q, qinv);
-  gs_st<4, true>(x, TwL{lt, 1}, q, qinv);
-  gs_st<8, false>(x, TwL{lt, 0}, q, qinv);
+  gs_st<1, kGs2.m[0]>(x, TwU{u.top + 7}, q, qinv);
+  gs_st<2, kGs2.m[1]>(x, TwU{u.top + 3}, q, qinv);
+  gs_st<4, kGs2.m[2]>(x, TwU{u.top + 1}, q, qinv);
+  gs_st<8, kGs2.m[3]>(x, TwU{u.top}, q, qinv);
   if constexpr (SINGLE) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) st(row, B + t + 256 * r, x[r], P);
@@ -829,14 +867,20 @@ struct KsCombine {
     const uint64_t* add2 = tab.add2[job];
     uint64_t* out = tab.out[job] + o;
     if (tab.fold) {
+      // |x| < 1.9 q, f < q: the product lies within (0.5 + 0.25 * 1.9) q, so
+      // |v| < 2 q, the product with h (and add2) again; a bare v + add2 may not
       const double2 h = qlinv ? qlinv[i] : double2{0.0, 0.0};
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const uint32_t k = k0 + 256 * r;
-        double v = u2d(pa.a[r]) - mm_shoup(x[r], f.x, f.y, q);  // |v| < 2.5 q
-        if (qlinv) v = mm_shoup(v, h.x, h.y, q);
-        if (add2) v += u2d(add2[o + k]);
-        out[k] = to_res(v, q, qinv);
+        double v = u2d(pa.a[r]) - mm_shoup(x[r], f.x, f.y, q);
+        if (qlinv) {
+          v = mm_shoup(v, h.x, h.y, q);
+          if (add2) v += u2d(add2[o + k]);
+          out[k] = to_res_2q(v, q, qinv);
+        } else {
+          out[k] = add2 ? to_res(v + u2d(add2[o + k]), q, qinv) : to_res_2q(v, q, qinv);
+        }
       }
       return;
     }
@@ -871,9 +915,8 @@ struct RsCombine {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const uint32_t k = k0 + 256 * r;
-      double v = mm_shoup(u2d(in[k]) - x[r], f.x, f.y, q);
-      if (add) v += u2d(add[o + k]);
-      out[k] = to_res(v, q, qinv);
+      const double v = mm_shoup(u2d(in[k]) - x[r], f.x, f.y, q);  // within 1.3 q
+      out[k] = add ? to_res(v + u2d(add[o + k]), q, qinv) : to_res_2q(v, q, qinv);
     }
   }
 };
@@ -883,7 +926,7 @@ namespace {
 hipError_t launch_fwd_outer(const Context* c, const RowSel& rs, uint32_t batch, uint32_t limbs,
                             hipStream_t s) {
   const dim3 grid(c->n / kBlock, batch, limbs), blk(kThreads);
-  const double2* tw = c->d_tw_fwd;
+  const double* tw = c->d_tw_fwd;
   switch (c->log_n) {
     case 12: return hipSuccess;
     case 13: hipLaunchKernelGGL(k_fwd_outer<1>, grid, blk, 0, s, rs, c->log_n, c->d_pk, tw); break;
@@ -899,7 +942,7 @@ template <class St>
 hipError_t launch_inv_outer(const Context* c, const RowSel& rs, uint32_t batch, uint32_t limbs,
                             const St& st, hipStream_t s) {
   const dim3 grid(c->n / kBlock, batch, limbs), blk(kThreads);
-  const double2* tw = c->d_tw_inv;
+  const double* tw = c->d_tw_inv;
   switch (c->log_n) {
     case 12: return hipSuccess;
     case 13: k_inv_outer<1, St><<<grid, blk, 0, s>>>(rs, c->log_n, c->d_pk, tw, st); break;
@@ -979,7 +1022,7 @@ template <int LOGM, class Map>
 hipError_t launch_bconv_logm(const Context* c, const Map& map, uint32_t targets, uint32_t groups,
                              hipStream_t s) {
   constexpr uint32_t M = 1u << LOGM;
-  const double2* tw = c->d_tw_fwd;
+  const double* tw = c->d_tw_fwd;
   if constexpr (kMfmaMap<Map>) {
     if (mfma_bytes(map) && map.alpha >= kMfmaMinDigit) {
       const uint32_t quads = (targets + 3) / 4, cols = 4 * M * groups;

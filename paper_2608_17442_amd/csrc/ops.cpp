@@ -30,6 +30,12 @@ uint64_t prod_mod_except(const std::vector<uint64_t>& ps, size_t skip, uint64_t 
 
 double2 entry(uint64_t v, uint64_t m) { return double2{(double)v, (double)v / (double)m}; }
 
+// the balanced representative: a product with it lands closer to zero
+double2 entry_bal(uint64_t v, uint64_t m) {
+  const double w = v > m / 2 ? -(double)(m - v) : (double)v;
+  return double2{w, w / (double)m};
+}
+
 // The 512 operand bytes of one target row of the matrix-core conversion
 // (LevelTables::mu_bytes): hats[a] for a < aj (aj <= 8), target prime m.
 void conversion_bytes(int8_t* dst, const uint64_t* hats, uint32_t aj, uint64_t m) {
@@ -66,7 +72,7 @@ const LevelTables* level_tables(Context* c, uint32_t level, int* err) {
     for (uint32_t a = 0; a < hi - lo; ++a) {
       const uint64_t inv = h_inv(prod_mod_except(dq, a, dq[a]), dq[a]);
       mu_inv[j * alpha + a] = entry(inv, dq[a]);
-      mu_inv_n[lo + a] = entry(h_mulmod(inv, h_inv(c->n % dq[a], dq[a]), dq[a]), dq[a]);
+      mu_inv_n[lo + a] = entry_bal(h_mulmod(inv, h_inv(c->n % dq[a], dq[a]), dq[a]), dq[a]);
       for (uint32_t row = 0; row < E; ++row) {
         const uint64_t m = ext_prime(row);
         mu_hat[((size_t)j * E + row) * alpha + a] = entry(prod_mod_except(dq, a, m), m);
@@ -85,7 +91,7 @@ const LevelTables* level_tables(Context* c, uint32_t level, int* err) {
   for (uint32_t a = 0; a < alpha; ++a) {
     const uint64_t inv = h_inv(prod_mod_except(ps, a, ps[a]), ps[a]);
     md_inv[a] = entry(inv, ps[a]);
-    md_inv_n[a] = entry(h_mulmod(inv, h_inv(c->n % ps[a], ps[a]), ps[a]), ps[a]);
+    md_inv_n[a] = entry_bal(h_mulmod(inv, h_inv(c->n % ps[a], ps[a]), ps[a]), ps[a]);
   }
   for (uint32_t i = 0; i < L; ++i) {
     const uint64_t q = c->primes[i];
@@ -106,15 +112,15 @@ const LevelTables* level_tables(Context* c, uint32_t level, int* err) {
       mr_hat((size_t)(level - 1) * (alpha + 1));
   {
     const uint64_t ql = c->primes[level - 1];
-    rs_ninv[0] = entry(h_inv(c->n % ql, ql), ql);
+    rs_ninv[0] = entry_bal(h_inv(c->n % ql, ql), ql);
     for (uint32_t i = 0; i < level; ++i) one[i] = entry(1, c->primes[i]);
     // m_0 = q_{level-1}: the inner product stores x P^-1 on that row, which is
     // already x (M/m_0)^-1, so its constant is N^-1 alone
-    mr_inv_n[0] = entry(h_inv(c->n % ql, ql), ql);
+    mr_inv_n[0] = entry_bal(h_inv(c->n % ql, ql), ql);
     for (uint32_t a = 0; a < alpha; ++a) {
       const uint64_t pa = ps[a];
       const uint64_t mh = h_mulmod(prod_mod_except(ps, a, pa), ql % pa, pa);  // M/p_a mod p_a
-      mr_inv_n[1 + a] = entry(h_mulmod(h_inv(mh, pa), h_inv(c->n % pa, pa), pa), pa);
+      mr_inv_n[1 + a] = entry_bal(h_mulmod(h_inv(mh, pa), h_inv(c->n % pa, pa), pa), pa);
     }
     for (uint32_t i = 0; i + 1 < level; ++i) {
       const uint64_t q = c->primes[i];
