@@ -12,8 +12,8 @@
 // encoded over Q u P, and takes one ModDown per c~_{b,p}.
 //
 // The pt-MAC streams every plaintext diagonal once.  A thread owns one
-// coefficient of one limb and accumulates G outputs (b, p) at a time, so each
-// baby-step value it loads is reused G times; the diagonals are read with
+// coefficient of one limb and accumulates G <= 16 outputs (b, p) at a time, so
+// each baby-step value it loads is reused G times; the diagonals are read with
 // coalesced loads and nothing else is written until the final sums.  Every
 // prime is below 2^50, so a diagonal bank stores each residue in 50 bits
 // (6.25 bytes instead of 8) as three word planes: the low 32 bits, bits
@@ -58,8 +58,7 @@ uint32_t galois_of_step(const Context* c, int32_t step);
 namespace {
 
 constexpr int kThreads = 256;  // also the coefficient tile of the diagonal bank
-constexpr int kGroup = 16;     // outputs accumulated per thread
-static_assert(kGroup % 16 == 0, "an output group covers whole top-bit words");
+constexpr uint32_t kGroup = 16;  // most outputs accumulated per thread
 
 // Diagonal bank.  For each (limb i, tile of kThreads coefficients, term t) a
 // record of bank_record_words(n_outputs) 32-bit words per coefficient, laid
@@ -108,19 +107,22 @@ struct PtLayout {
 typedef __attribute__((address_space(1))) const uint64_t gcu64;
 typedef __attribute__((address_space(1))) uint64_t gu64;
 
-template <int G, bool BANK>
-__global__ __launch_bounds__(kThreads) void k_ptmac(const uint64_t* const* __restrict__ baby,
-                                                    const uint64_t* const* __restrict__ diag,
-                                                    const uint32_t* __restrict__ bank,
-                                                    uint64_t* const* __restrict__ outs,
-                                                    uint32_t n_outputs, uint32_t terms,
-                                                    uint32_t n, uint32_t limbs,
-                                                    const PrimeK* __restrict__ pk, PtLayout lay) {
+// Grid over (coefficient tile, limb, output group).  W == 0: a workgroup takes
+// a tile of kThreads coefficients, every wavefront all the terms.  W > 0: W
+// wavefronts share the terms of 64 coefficients and add their sums through LDS
+// (the sums are exact integers, so the split does not change the result).
+// Outputs o0 .. o0 + G - 1 of a group: G is 1, 2 or 4 (one group), 8, 12 or 16.
+template <int G, bool BANK, int W>
+__global__ __launch_bounds__(W ? 64 * W : kThreads) void k_ptmac(
+    const uint64_t* const* __restrict__ baby, const uint64_t* const* __restrict__ diag,
+    const uint32_t* __restrict__ bank, uint64_t* const* __restrict__ outs, uint32_t n_outputs,
+    uint32_t terms, uint32_t n, uint32_t limbs, const PrimeK* __restrict__ pk, PtLayout lay) {
   // 1-D grid over (coefficient tile, limb, output group).  Workgroups are
   // dealt to the 8 XCDs round-robin; the decode keeps all output groups of one
   // tile on the same XCD and adjacent in time, so the tile's baby-step values
   // (read once per group) come from that XCD's L2 instead of HBM.
-  const uint32_t tiles = n / kThreads, n_groups = (n_outputs + G - 1) / G;
+  constexpr uint32_t kTile = W ? 64 : kThreads;
+  const uint32_t tiles = n / kTile, n_groups = (n_outputs + G - 1) / G;
   const uint32_t total_tiles = tiles * limbs;
   uint32_t tile_lin, grp;
   if ((total_tiles & 7u) == 0) {
@@ -131,16 +133,23 @@ __global__ __launch_bounds__(kThreads) void k_ptmac(const uint64_t* const* __res
     grp = blockIdx.x % n_groups;
     tile_lin = blockIdx.x / n_groups;
   }
-  const uint32_t i = tile_lin / tiles, tile = tile_lin % tiles;
-  const uint32_t k = tile * kThreads + threadIdx.x;
+  const uint32_t i = tile_lin / tiles;
+  const uint32_t lane = W ? threadIdx.x & 63u : threadIdx.x;
+  // the wavefront's first term and stride (uniform, so that the pointers of a
+  // term are scalar loads)
+  const uint32_t wave = W ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0u;
+  const uint32_t step = W ? W : 1;
+  const uint32_t kb = (tile_lin % tiles) * kTile;  // first coefficient (uniform)
   const uint32_t o0 = grp * G;
-  if (i >= limbs) return;
   const PrimeK P = pk[i < lay.split ? i : lay.prime1 + (i - lay.split)];
   const uint32_t g_end = min((uint32_t)G, n_outputs - o0);
   double a0[G], a1[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) a0[g] = a1[g] = 0.0;
-  const size_t pi = (size_t)i * n + k, c0 = (size_t)i * lay.row_stride + k,
+  // Addresses are a uniform base (scalar registers) plus the lane: with one
+  // vector address per plane the 16-output kernel took 158 registers and ran
+  // three wavefronts per SIMD.
+  const size_t pi = (size_t)i * n + kb, c0 = (size_t)i * lay.row_stride + kb,
                c1 = c0 + lay.comp_stride;
   // Outputs past the end of a partial group re-read the group's last valid
   // diagonal (results discarded at the store), which keeps the loop body free
@@ -148,48 +157,62 @@ __global__ __launch_bounds__(kThreads) void k_ptmac(const uint64_t* const* __res
   uint32_t og[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) og[g] = min((uint32_t)g, g_end - 1);
-  // bank: this thread's words of record (i, tile, 0); the planes of the group
+  // bank: the wavefront's words of record (i, tile, 0); the planes of the group.
+  // o0 is even (or 0): output o0 + g sits in hi word g / 2 of the group's; its
+  // top word is the group's first or, from output kTop on, its second
+  constexpr int GH = (G + 1) / 2;
+  const uint32_t top0 = o0 >> 4;
   const uint32_t* bk =
-      BANK ? bank + bank_record(i, tile, 0, n, n_outputs, terms) + threadIdx.x : nullptr;
+      BANK ? bank + bank_record(i, kb / kThreads, 0, n, n_outputs, terms) + kb % kThreads : nullptr;
   const size_t rec_stride = (size_t)bank_record_words(n_outputs) * kThreads;
   const uint32_t hi_plane = n_outputs, top_plane = n_outputs + bank_hi_planes(n_outputs);
-  for (uint32_t t = 0; t < terms; ++t) {
-    const gcu64* bp = (const gcu64*)baby[t];
-    const double x0 = u2d(bp[c0]), x1 = u2d(bp[c1]);
+  // up to 12 outputs the next term's pointer is read a term ahead (at 16 its
+  // registers cost more than the wait: 9.58 against 9.46 ms for 96 outputs of
+  // 32 terms, N = 2^16, 16 limbs; 24 outputs of 192 terms: 12.99 against 13.14)
+  constexpr bool kAhead = G < 16;
+  const gcu64* next = kAhead ? (const gcu64*)baby[min(wave, terms - 1)] : nullptr;
+#pragma unroll 1
+  for (uint32_t t = wave; t < terms; t += step) {
+    const gcu64* bp = kAhead ? next : (const gcu64*)baby[t];
+    if constexpr (kAhead) next = (const gcu64*)baby[min(t + step, terms - 1)];
+    const double x0 = u2d((bp + c0)[lane]), x1 = u2d((bp + c1)[lane]);
     double w[G];
     if (BANK) {
       // every bank word streams past once (non-temporal loads), so that the
       // bank does not evict the baby-step values the tile's other output
       // groups re-read
       const uint32_t* rec = bk + (size_t)t * rec_stride;
-      uint32_t lo[G], hw[G / 2], tw[G / 16];
+      uint32_t lo[G], hw[GH], tw[2];
 #pragma unroll
       for (int g = 0; g < G; ++g)
-        lo[g] = __builtin_nontemporal_load(rec + (size_t)(o0 + og[g]) * kThreads);
+        lo[g] = __builtin_nontemporal_load(rec + (size_t)(o0 + og[g]) * kThreads + lane);
 #pragma unroll
-      for (int j = 0; j < G / 2; ++j)
-        hw[j] = __builtin_nontemporal_load(rec + (size_t)(hi_plane + ((o0 + og[2 * j]) >> 1)) *
-                                                     kThreads);
+      for (int j = 0; j < GH; ++j)
+        hw[j] = __builtin_nontemporal_load(
+            rec + (size_t)(hi_plane + ((o0 + og[2 * j]) >> 1)) * kThreads + lane);
+      tw[0] = __builtin_nontemporal_load(rec + (size_t)(top_plane + top0) * kThreads + lane);
+      // only a group of 12 can reach into a second top word
+      tw[1] = G == 12 ? __builtin_nontemporal_load(
+                            rec + (size_t)(top_plane + ((o0 + g_end - 1) >> 4)) * kThreads + lane)
+                      : 0u;
 #pragma unroll
-      for (int m = 0; m < G / 16; ++m)
-        tw[m] = __builtin_nontemporal_load(rec + (size_t)(top_plane + ((o0 + og[16 * m]) >> 4)) *
-                                                     kThreads);
-      // o0 is a multiple of 16: output o0 + og[g] sits at half og[g] & 1 of its
-      // hi word and at bit 2 (og[g] & 15) of its top word
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-        w[g] = bank_value(lo[g], hw[g / 2], 16u * (og[g] & 1u), tw[g / 16], 2u * (og[g] & 15u));
+      for (int g = 0; g < G; ++g) {
+        // groups of 16 and lone groups start at a multiple of 16
+        const uint32_t o = (G == 12 ? o0 : 0u) + og[g];
+        const uint32_t top = G == 12 && (o >> 4) != top0 ? tw[1] : tw[0];
+        w[g] = bank_value(lo[g], hw[g / 2], 16u * (og[g] & 1u), top, 2u * (o & 15u));
+      }
     } else {
 #pragma unroll
       for (int g = 0; g < G; ++g)
-        w[g] = u2d(((const gcu64*)diag[(size_t)(o0 + og[g]) * terms + t])[pi]);
+        w[g] = u2d(((const gcu64*)diag[(size_t)(o0 + og[g]) * terms + t] + pi)[lane]);
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       a0[g] += mm_var(x0, w[g], P.q, P.qinv);
       a1[g] += mm_var(x1, w[g], P.q, P.qinv);
     }
-    if ((t & 3) == 3) {
+    if (((t / step) & 3) == 3) {
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         a0[g] = red_bal(a0[g], P.q, P.qinv);
@@ -197,12 +220,34 @@ __global__ __launch_bounds__(kThreads) void k_ptmac(const uint64_t* const* __res
       }
     }
   }
+  if constexpr (W == 0) {
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    if ((uint32_t)g < g_end) {
-      gu64* o = (gu64*)outs[o0 + g];
-      o[c0] = to_res(a0[g], P.q, P.qinv);
-      o[c1] = to_res(a1[g], P.q, P.qinv);
+    for (int g = 0; g < G; ++g) {
+      if ((uint32_t)g < g_end) {
+        gu64* o = (gu64*)outs[o0 + g];
+        (o + c0)[lane] = to_res(a0[g], P.q, P.qinv);
+        (o + c1)[lane] = to_res(a1[g], P.q, P.qinv);
+      }
+    }
+  } else {
+    // sums [row = 2 g + component][wave][lane], each within q / 2; wavefront w
+    // adds up rows w, w + W, ... (eight halves before a reduction: below 5 q)
+    __shared__ double part[2 * G * W * 64];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      part[((2 * g) * W + wave) * 64 + lane] = red_bal(a0[g], P.q, P.qinv);
+      part[((2 * g + 1) * W + wave) * 64 + lane] = red_bal(a1[g], P.q, P.qinv);
+    }
+    __syncthreads();
+    for (uint32_t r = wave; r < 2 * g_end; r += W) {
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        s += part[(r * W + w) * 64 + lane];
+        if (w == 7) s = red_bal(s, P.q, P.qinv);
+      }
+      gu64* o = (gu64*)outs[o0 + r / 2];
+      (o + (r & 1u ? c1 : c0))[lane] = to_res(s, P.q, P.qinv);
     }
   }
 }
@@ -296,6 +341,65 @@ __global__ __launch_bounds__(kThreads) void k_bsgs_slots(const double* __restric
     }
   }
   z[(size_t)blockIdx.y * S.n_slots + j] = double2{re, im};
+}
+
+struct PtArgs {
+  const uint64_t* const* baby;
+  const uint64_t* const* diag;  // table of plaintexts, or null: the bank
+  const uint32_t* bank;
+  uint64_t* const* outs;
+  uint32_t n_outputs, terms, n, rows;
+  const PrimeK* pk;
+  PtLayout lay;
+};
+
+template <int G, int W>
+void ptmac_run(const PtArgs& a, hipStream_t s) {
+  const uint32_t tile = W ? 64 : kThreads, threads = W ? 64 * W : kThreads;
+  const dim3 grid((a.n / tile) * a.rows * ((a.n_outputs + G - 1) / G));
+  if (a.bank)
+    k_ptmac<G, true, W><<<grid, threads, 0, s>>>(a.baby, a.diag, a.bank, a.outs, a.n_outputs,
+                                                 a.terms, a.n, a.rows, a.pk, a.lay);
+  else
+    k_ptmac<G, false, W><<<grid, threads, 0, s>>>(a.baby, a.diag, a.bank, a.outs, a.n_outputs,
+                                                  a.terms, a.n, a.rows, a.pk, a.lay);
+}
+
+// One pt-MAC.  The outputs are dealt evenly to the fewest groups of at most 16,
+// so that few threads compute outputs that nobody stores: 24 outputs of 192
+// terms (N = 2^16, 16 limbs, 30 GB bank) as two groups of 12 take 5.51 ms
+// (5.5 TB/s), as 16 + 8 of 16 6.62 ms; one output of 64 terms over the whole
+// call 1.66 -> 1.43 ms.  A launch with fewer than kPtFill wavefronts (two per
+// SIMD) is bound by the latency of its serial terms: their sum is then split
+// over the wavefronts of a workgroup, as far as each keeps two terms and the
+// partial sums fit in 32 KB of LDS: 64 terms of one output at N = 2^12, three
+// limbs, 71 -> 5.4 us.
+constexpr uint32_t kPtFill = 2048;
+hipError_t launch_ptmac(const PtArgs& a, hipStream_t s) {
+  const uint32_t groups = (a.n_outputs + kGroup - 1) / kGroup;
+  const uint32_t per = (a.n_outputs + groups - 1) / groups;
+  const uint32_t waves = (a.n / 64) * a.rows * groups;
+  const bool split = waves < kPtFill;
+  if (per <= 1) {
+    if (split && a.terms >= 32) ptmac_run<1, 16>(a, s);
+    else if (split && a.terms >= 8) ptmac_run<1, 4>(a, s);
+    else ptmac_run<1, 0>(a, s);
+  } else if (per <= 2) {
+    if (split && a.terms >= 32) ptmac_run<2, 16>(a, s);
+    else if (split && a.terms >= 8) ptmac_run<2, 4>(a, s);
+    else ptmac_run<2, 0>(a, s);
+  } else if (per <= 4) {
+    if (split && a.terms >= 8) ptmac_run<4, 4>(a, s);
+    else ptmac_run<4, 0>(a, s);
+  } else if (per <= 8) {
+    if (split && a.terms >= 8) ptmac_run<8, 4>(a, s);
+    else ptmac_run<8, 0>(a, s);
+  } else if (per <= 12) {
+    ptmac_run<12, 0>(a, s);
+  } else {
+    ptmac_run<16, 0>(a, s);
+  }
+  return hipGetLastError();
 }
 
 #define HIPCK(expr)                                   \
@@ -473,16 +577,9 @@ int ptct_matvec(Context* c, fesc_matvec_plan* p, const uint64_t* const* in,
   const uint32_t n_outputs = d.n_out * d.n2;
   const PtLayout lay = lazy ? PtLayout{(uint32_t)n, rows * (uint32_t)n, level, c->L}
                             : PtLayout{2 * (uint32_t)n, (uint32_t)n, level, c->L};
-  dim3 grid((c->n / kThreads) * rows * ((n_outputs + kGroup - 1) / kGroup));
-  if (p->bank)
-    hipLaunchKernelGGL((k_ptmac<kGroup, true>), grid, dim3(kThreads), 0, s, p->d_baby,
-                       (const uint64_t* const*)nullptr, p->bank, p->d_ct, n_outputs,
-                       (uint32_t)n_baby, c->n, rows, c->d_pk, lay);
-  else
-    hipLaunchKernelGGL((k_ptmac<kGroup, false>), grid, dim3(kThreads), 0, s, p->d_baby,
-                       p->d_diag, (const uint32_t*)nullptr, p->d_ct, n_outputs,
-                       (uint32_t)n_baby, c->n, rows, c->d_pk, lay);
-  HIPCK(hipGetLastError());
+  HIPCK(launch_ptmac(PtArgs{p->d_baby, p->d_diag, p->bank, p->d_ct, n_outputs, (uint32_t)n_baby,
+                            c->n, rows, c->d_pk, lay},
+                     s));
   if (lazy) {
     // one ModDown per c~_{b,p}, into the ciphertext regions
     std::vector<uint64_t*> cts(n_outputs);
@@ -649,18 +746,10 @@ int ptct_matvec_many(Context* c, fesc_matvec_plan* p, uint32_t count, const uint
     // pt-MAC per vector
     const uint32_t rows = diag_rows(c, d);
     const PtLayout lay{2 * (uint32_t)n, (uint32_t)n, level, c->L};
-    const dim3 grid((c->n / kThreads) * rows * ((n2 + kGroup - 1) / kGroup));
-    for (uint32_t v = 0; v < nb; ++v) {
-      if (p->bank)
-        hipLaunchKernelGGL((k_ptmac<kGroup, true>), grid, dim3(kThreads), 0, s,
-                           p->d_mbaby + (size_t)v * n1, (const uint64_t* const*)nullptr, p->bank,
-                           p->d_mct + (size_t)v * n2, n2, n1, c->n, rows, c->d_pk, lay);
-      else
-        hipLaunchKernelGGL((k_ptmac<kGroup, false>), grid, dim3(kThreads), 0, s,
-                           p->d_mbaby + (size_t)v * n1, p->d_diag, (const uint32_t*)nullptr,
-                           p->d_mct + (size_t)v * n2, n2, n1, c->n, rows, c->d_pk, lay);
-      HIPCK(hipGetLastError());
-    }
+    for (uint32_t v = 0; v < nb; ++v)
+      HIPCK(launch_ptmac(PtArgs{p->d_mbaby + (size_t)v * n1, p->d_diag, p->bank,
+                                p->d_mct + (size_t)v * n2, n2, n1, c->n, rows, c->d_pk, lay},
+                         s));
     // giant steps (as in ptct_matvec)
     std::vector<const uint64_t*> gin;
     std::vector<uint64_t*> gout;
