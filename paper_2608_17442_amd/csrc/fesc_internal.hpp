@@ -210,6 +210,8 @@ struct RowSel {
 // kernel launchers (ntt.hip)
 hipError_t launch_ntt_rows(const Context* c, const RowSel& rs, uint32_t batch, uint32_t limbs,
                            bool inverse, hipStream_t s);
+hipError_t launch_ntt_inv_from(const Context* c, const uint64_t* in, uint64_t* out, uint32_t batch,
+                               uint32_t limbs, hipStream_t s);
 hipError_t launch_ntt(const Context* c, uint64_t* d, uint32_t batch, size_t batch_stride,
                       uint32_t limbs, size_t limb_stride, uint32_t prime0, bool inverse,
                       hipStream_t s);

@@ -745,6 +745,17 @@ struct LoadRow {
   }
 };
 
+// Source of the inverse inner pass: rows [blockIdx.y][blockIdx.z][N] of a buffer
+// (out of place).
+struct LoadFrom {
+  const uint64_t* in;
+  uint32_t rows, n;
+  __device__ __forceinline__ void operator()(const uint64_t*, uint32_t off, double (&x)[16],
+                                             double, double) const {
+    load16(in + ((size_t)blockIdx.y * rows + blockIdx.z) * n + off, x);
+  }
+};
+
 // Source of the inverse inner pass: row blockIdx.z of source blockIdx.y of a
 // key-switch table (out of place; the row receives the result).  A product
 // source (src_y set) is formed here, x y mod q in (-q/2, q/2] (balanced
@@ -1169,6 +1180,13 @@ hipError_t launch_ntt_rows(const Context* c, const RowSel& rs, uint32_t batch, u
   hipError_t e = launch_fwd_outer(c, rs, batch, limbs, s);
   if (e != hipSuccess) return e;
   return launch_fwd_inner(c, rs, batch, limbs, StoreResidues{}, s);
+}
+
+// Inverse transform of in[batch][limbs][N] into out (primes 0 .. limbs - 1).
+hipError_t launch_ntt_inv_from(const Context* c, const uint64_t* in, uint64_t* out, uint32_t batch,
+                               uint32_t limbs, hipStream_t s) {
+  RowSel rs{out, (size_t)limbs * c->n, (size_t)c->n, 0, limbs, 0, 0, 0, 0};
+  return launch_inverse(c, rs, batch, limbs, LoadFrom{in, limbs, c->n}, InvCanon{}, s);
 }
 
 hipError_t launch_ntt(const Context* c, uint64_t* d, uint32_t batch, size_t batch_stride,

@@ -14,7 +14,7 @@ import synth
 from oracle import ckks as C
 from oracle import encoding as E
 from paper_2608_17442_amd import fesc as F
-from tests.gpu_helpers import need_gpu, step, to_host
+from tests.gpu_helpers import need_gpu, step, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -163,3 +163,34 @@ def test_decode_plain_errors():
     ctx.decode_plain(pt, 0, 3, 1.0, out)           # nothing to do
     ctx.decode_plain(pt, 1, 3, 1.0, out)
     assert torch.count_nonzero(out).item() == 0    # the zero plaintext decodes to zeros
+
+
+# Every register bucket of the CRT (levels 1..32 in steps of 4), past it (33
+# limbs), primes too far apart for it, one row (N = 4096) and 1, 2, 4, 8 of them
+@pytest.mark.parametrize("log_n,bits,level,count", [
+    (12, (50,), 3, 2), (12, (30,), 33, 1), (12, (30,), 32, 1), (12, (36, 30, 50), 6, 1),
+    (13, (30,), 5, 3), (13, (50, 30), 7, 2), (13, (36,), 12, 1), (14, (45,), 10, 2),
+    (14, (36,), 21, 1), (15, (50,), 20, 2), (15, (36,), 27, 1), (16, (36,), 2, 2),
+])
+def test_decode_plain_full_range(log_n, bits, level, count):
+    """Uniform residues: coefficients over the whole of (-Q/2, Q/2], decoded at
+    scale Q.  Both sides' coefficients are exact integers rounded to doubles (one
+    rounding per level here, relative to a sum that grows by a prime each
+    time: 2^-52), and the transforms' sums add about 2^-53 log2 N each."""
+    count_of = {b: -(-level // len(bits)) for b in bits}
+    by = {b: C.find_primes(log_n, b, k + 4) for b, k in count_of.items()}
+    qs = [by[bits[i % len(bits)]][i // len(bits)] for i in range(level)]
+    P = C.Params(log_n, qs, by[bits[0]][-4:])
+    ctx = F.Context(log_n, P.q, P.p)
+    n = P.n
+    pth = np.stack([synth.uniform_residues(51, "dec", qs, n, b) for b in range(count)])
+    Q = 1
+    for q in qs:
+        Q *= q
+    out = torch.zeros(count, n // 2, dtype=torch.complex128, device="cuda")
+    step(f"decode_plain N=2^{log_n} level={level} bits={bits}")
+    ctx.decode_plain(to_dev(pth).reshape(-1), count, level, float(Q), out)
+    got = out.cpu().numpy()
+    for b in range(count):
+        want = C.decode_plain(P, pth[b], float(Q))
+        assert np.linalg.norm(got[b] - want) <= 1e-14 * np.linalg.norm(want)
