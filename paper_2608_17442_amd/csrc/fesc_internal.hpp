@@ -158,6 +158,11 @@ struct Context {
   // map (position p of the length-N transform input holds z_j if inv[p] = j,
   // conj(z_j) if inv[p] = ~j)
   double2* d_enc_tw = nullptr;
+  // its entries that the encoder's 4096-point row DFT uses, in the order of use:
+  // for the steps on position bits 11..8, 7..4, 3..0 (thread positions p < 256,
+  // 16, 1) [15][p]: entry H - 1 + r (H = 1, 2, 4, 8; r < H) at p is
+  // T[(p + P r) N / (P H)], P the number of positions
+  double2* d_enc_row = nullptr;
   int32_t* d_enc_inv = nullptr;
   // device decoding's mixed-radix CRT: [L][L], entry [i][j] (j < i) =
   // q_j^-1 mod q_i as {w, w / q_i}, w the balanced representative

@@ -223,6 +223,12 @@ static int build_tables(Context* c) {
     const double ang = -M_PI * (double)k / (double)n;
     enc_tw[k] = double2{std::cos(ang), std::sin(ang)};
   }
+  std::vector<double2> enc_row;
+  for (uint32_t p = 256; p >= 1; p /= 16)
+    for (uint32_t h = 1; h <= 8; h *= 2)
+      for (uint32_t r = 0; r < h; ++r)
+        for (uint32_t k = 0; k < p; ++k)
+          enc_row.push_back(enc_tw[(size_t)(k + p * r) * (n / (p * h))]);
   std::vector<int32_t> enc_inv(n);
   {
     uint64_t e = 1;
@@ -246,7 +252,10 @@ static int build_tables(Context* c) {
                                 hipMemcpyHostToDevice), "hipMemcpy")))
     return rc == FESC_ERR_HIP ? fail(FESC_ERR_OOM, "decoding table allocation failed") : rc;
   if ((rc = hip_check(hipMalloc(&c->d_enc_tw, sizeof(double2) * enc_tw.size()), "hipMalloc")) ||
+      (rc = hip_check(hipMalloc(&c->d_enc_row, sizeof(double2) * enc_row.size()), "hipMalloc")) ||
       (rc = hip_check(hipMalloc(&c->d_enc_inv, sizeof(int32_t) * enc_inv.size()), "hipMalloc")) ||
+      (rc = hip_check(hipMemcpy(c->d_enc_row, enc_row.data(), sizeof(double2) * enc_row.size(),
+                                hipMemcpyHostToDevice), "hipMemcpy")) ||
       (rc = hip_check(hipMemcpy(c->d_enc_tw, enc_tw.data(), sizeof(double2) * enc_tw.size(),
                                 hipMemcpyHostToDevice), "hipMemcpy")) ||
       (rc = hip_check(hipMemcpy(c->d_enc_inv, enc_inv.data(), sizeof(int32_t) * enc_inv.size(),
@@ -283,6 +292,7 @@ void destroy(Context* c) {
   (void)hipFree(c->d_tw3_fwd);
   (void)hipFree(c->d_tw3_inv);
   (void)hipFree(c->d_enc_tw);
+  (void)hipFree(c->d_enc_row);
   (void)hipFree(c->d_enc_inv);
   (void)hipFree(c->d_garner);
   (void)hipFree(c->scratch);

@@ -194,3 +194,35 @@ def test_decode_plain_full_range(log_n, bits, level, count):
     for b in range(count):
         want = C.decode_plain(P, pth[b], float(Q))
         assert np.linalg.norm(got[b] - want) <= 1e-14 * np.linalg.norm(want)
+
+
+# Every split of the fused lift (one row at N = 4096, 1 .. 4 stages in its pass),
+# coefficients below and past 2^51, which are lifted by different code, and both
+# in one plaintext; counts that take one or several rows of limbs per workgroup
+@pytest.mark.parametrize("log_n,bits,level,count,log_scale", [
+    (12, 50, 3, 2, 58), (13, 36, 5, 3, 40), (13, 50, 3, 1, 60), (14, 45, 4, 70, 44),
+    (14, 50, 7, 1, 59), (15, 50, 5, 40, 40), (15, 36, 6, 2, 61), (16, 50, 3, 2, 62),
+])
+def test_encode_plain_lift(log_n, bits, level, count, log_scale):
+    """Every limb is the exact transform of one integer vector (its centred CRT),
+    and that vector is the real coefficients rounded: off by half a unit plus the
+    transforms' error, 8 est as above."""
+    P = C.params_small(log_n, bits, level, -(-level // 16))
+    ctx = F.Context(log_n, P.q, P.p)
+    n, qs = P.n, P.qs(level)
+    zs = np.stack([_slots(60 + b % 3, n // 2) for b in range(count)])
+    if log_scale > 51:
+        zs *= np.where(np.arange(count) % 2, 1.0, 2.0 ** (50 - log_scale))[:, None]
+        # a single slot: coefficients of modulus 2 Delta / N everywhere
+        zs[-1] = 0
+        zs[-1, 5] = 1.0
+    pt = torch.zeros(count * level * n, dtype=torch.int64, device="cuda")
+    step(f"encode_plain N=2^{log_n} level={level} count={count} scale=2^{log_scale}")
+    ctx.encode_plain(torch.from_numpy(zs).cuda(), 2.0 ** log_scale, pt, level)
+    got = to_host(pt).reshape(count, level, n)
+    for b in sorted({0, 1 % count, count - 1}):
+        m = E.crt_centered(C.intt(P, got[b], qs), qs).astype(np.int64)
+        raw = E.encode_real_coeffs(zs[b], 2.0 ** log_scale, n)
+        est = 2.0 ** (log_scale - 53) * log_n * np.sqrt(np.mean(np.abs(zs[b]) ** 2) / n)
+        assert np.max(np.abs(m - raw)) <= 0.5 + 8 * est + np.max(np.abs(raw)) * 2.0 ** -52
+        assert np.array_equal(got[b], C.ntt(P, C.lift(m, qs), qs)), b
