@@ -201,7 +201,7 @@ def test_decode_plain_full_range(log_n, bits, level, count):
 # in one plaintext; counts that take one or several rows of limbs per workgroup
 @pytest.mark.parametrize("log_n,bits,level,count,log_scale", [
     (12, 50, 3, 2, 58), (13, 36, 5, 3, 40), (13, 50, 3, 1, 60), (14, 45, 4, 70, 44),
-    (14, 50, 7, 1, 59), (15, 50, 5, 40, 40), (15, 36, 6, 2, 61), (16, 50, 3, 2, 62),
+    (14, 50, 7, 1, 59), (15, 50, 5, 40, 40), (15, 36, 6, 2, 61), (16, 50, 3, 2, 61),
 ])
 def test_encode_plain_lift(log_n, bits, level, count, log_scale):
     """Every limb is the exact transform of one integer vector (its centred CRT),
