@@ -858,12 +858,20 @@ struct KsCombine {
   uint32_t level, alpha, log_n;
   struct Pre {
     uint64_t a[16];  // acc[u][i] at k0 + 256 r
+    uint64_t b[16];  // add2[i][t] there, if given
   };
   __device__ __forceinline__ Pre pre(uint32_t k0, uint32_t n) const {
-    const uint64_t* a = acc + ((size_t)blockIdx.y * (level + alpha) + blockIdx.z) * n + k0;
+    const uint32_t u = blockIdx.y, i = blockIdx.z;
+    const uint64_t* a = acc + ((size_t)u * (level + alpha) + i) * n + k0;
+    const uint64_t* add2 = tab.add2[u >> 1];
     Pre p;
 #pragma unroll
     for (int r = 0; r < 16; ++r) p.a[r] = a[256 * r];
+    if (add2) {
+      add2 += ((size_t)2 * i + (u & 1)) * n + k0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p.b[r] = add2[256 * r];
+    }
     return p;
   }
   __device__ __forceinline__ void operator()(uint64_t*, uint32_t k0, const double (&x)[16],
@@ -887,10 +895,10 @@ struct KsCombine {
         double v = u2d(pa.a[r]) - mm_shoup(x[r], f.x, f.y, q);
         if (qlinv) {
           v = mm_shoup(v, h.x, h.y, q);
-          if (add2) v += u2d(add2[o + k]);
+          if (add2) v += u2d(pa.b[r]);
           out[k] = to_res_2q(v, q, qinv);
         } else {
-          out[k] = add2 ? to_res(v + u2d(add2[o + k]), q, qinv) : to_res_2q(v, q, qinv);
+          out[k] = add2 ? to_res(v + u2d(pa.b[r]), q, qinv) : to_res_2q(v, q, qinv);
         }
       }
       return;
@@ -900,7 +908,7 @@ struct KsCombine {
       const uint32_t k = k0 + 256 * r;
       double v = mm_shoup(u2d(pa.a[r]) - x[r], f.x, f.y, q);
       if (use_add) v += u2d(add[g ? galois_src(k, g, log_n) : k]);
-      if (add2) v += u2d(add2[o + k]);
+      if (add2) v += u2d(pa.b[r]);
       out[k] = to_res(v, q, qinv);
     }
   }
@@ -913,21 +921,33 @@ struct KsCombine {
 struct RsCombine {
   RsTable tab;
   const double2* qlinv;
-  using Pre = NoPre;
-  __device__ __forceinline__ Pre pre(uint32_t, uint32_t) const { return {}; }
+  struct Pre {
+    uint64_t in[16], add[16];  // in_b[i][t], add_b[i][t] at k0 + 256 r
+  };
+  __device__ __forceinline__ Pre pre(uint32_t k0, uint32_t n) const {
+    const uint32_t u = blockIdx.y, i = blockIdx.z, b = u >> 1, t = u & 1;
+    const size_t o = ((size_t)2 * i + t) * n + k0;
+    const uint64_t *in = tab.in[b] + o, *add = tab.add[b];
+    Pre p;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p.in[r] = in[256 * r];
+    if (add) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p.add[r] = (add + o)[256 * r];
+    }
+    return p;
+  }
   __device__ __forceinline__ void operator()(uint64_t*, uint32_t k0, const double (&x)[16],
-                                             double q, double qinv, uint32_t n, Pre) const {
+                                             double q, double qinv, uint32_t n,
+                                             const Pre& p) const {
     const uint32_t u = blockIdx.y, i = blockIdx.z, b = u >> 1, t = u & 1;
     const double2 f = qlinv[i];
-    const size_t o = ((size_t)2 * i + t) * n;
-    const uint64_t* in = tab.in[b] + o;
-    const uint64_t* add = tab.add[b];
-    uint64_t* out = tab.out[b] + o;
+    uint64_t* out = tab.out[b] + ((size_t)2 * i + t) * n + k0;
+    const bool add = tab.add[b];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const uint32_t k = k0 + 256 * r;
-      const double v = mm_shoup(u2d(in[k]) - x[r], f.x, f.y, q);  // within 1.3 q
-      out[k] = add ? to_res(v + u2d(add[o + k]), q, qinv) : to_res_2q(v, q, qinv);
+      const double v = mm_shoup(u2d(p.in[r]) - x[r], f.x, f.y, q);  // within 1.3 q
+      out[256 * r] = add ? to_res(v + u2d(p.add[r]), q, qinv) : to_res_2q(v, q, qinv);
     }
   }
 };
