@@ -226,26 +226,12 @@ struct InvDigit {
   }
 };
 
-// Inverse: stages in reverse order (sums reduced as kGsOut says), then the final
-// store (N^-1 scaling included).
-template <int LOGM, class St>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_inv_outer(RowSel rs, uint32_t log_n,
-                                                        const PrimeK* __restrict__ pk,
-                                                        const double* __restrict__ twi, St st) {
+// The inverse stages of the outer pass on the columns x[j M + m], in reverse
+// order (sums reduced as kGsOut says).
+template <int LOGM>
+__device__ __forceinline__ void inv_columns(double (&x)[16], const double* __restrict__ tw,
+                                            double q, double qinv) {
   constexpr int M = 1 << LOGM, C = 16 / M;
-  if (rs.skip()) return;
-  const uint32_t n = 1u << log_n;
-  const uint32_t prime = rs.prime();
-  const PrimeK P = pk[prime];
-  const double* tw = twi + (size_t)prime * n;
-  uint64_t* row = rs.row();
-  const double* rowd = reinterpret_cast<const double*>(row);
-  const uint32_t c0 = blockIdx.x * (kThreads * C) + threadIdx.x;
-  double x[16];
-#pragma unroll
-  for (int j = 0; j < C; ++j)
-#pragma unroll
-    for (int m = 0; m < M; ++m) x[j * M + m] = rowd[c0 + kThreads * j + kBlock * m];
 #pragma unroll
   for (int s = LOGM - 1; s >= 0; --s) {
     const int H = M >> (s + 1);
@@ -256,13 +242,32 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
 #pragma unroll
       for (int j = 0; j < C; ++j) {
         const double u = x[j * M + m], v = x[j * M + m + H];
-        // the plan's registers have M = 16 columns' stride: register m here
-        x[j * M + m] =
-            (kGsOut.m[LOGM - 1 - s] >> m) & 1u ? red_bal(u + v, P.q, P.qinv) : u + v;
-        x[j * M + m + H] = mm_var(u - v, w, P.q, P.qinv);
+        x[j * M + m] = (kGsOut.m[LOGM - 1 - s] >> m) & 1u ? red_bal(u + v, q, qinv) : u + v;
+        x[j * M + m + H] = mm_var(u - v, w, q, qinv);
       }
     }
   }
+}
+
+// Inverse: the columns, then the final store (N^-1 scaling included).
+template <int LOGM, class St>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_inv_outer(
+    RowSel rs, uint32_t log_n, const PrimeK* __restrict__ pk, const double* __restrict__ twi,
+    St st) {
+  constexpr int M = 1 << LOGM, C = 16 / M;
+  if (rs.skip()) return;
+  const uint32_t n = 1u << log_n;
+  const uint32_t prime = rs.prime();
+  const PrimeK P = pk[prime];
+  uint64_t* row = rs.row();
+  const double* rowd = reinterpret_cast<const double*>(row);
+  const uint32_t c0 = blockIdx.x * (kThreads * C) + threadIdx.x;
+  double x[16];
+#pragma unroll
+  for (int j = 0; j < C; ++j)
+#pragma unroll
+    for (int m = 0; m < M; ++m) x[j * M + m] = rowd[c0 + kThreads * j + kBlock * m];
+  inv_columns<LOGM>(x, twi + (size_t)prime * n, P.q, P.qinv);
 #pragma unroll
   for (int j = 0; j < C; ++j)
 #pragma unroll
@@ -278,14 +283,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
 // x_a the centred digits stored by the inverse transform (InvDigit, fp64).
 // The first log M forward stages then run on the thread's columns exactly as
 // in k_fwd_outer and the fp64 intermediate is stored; for M = 1 (no outer
-// pass) the canonical residue is stored instead.  Targets vary fastest after
+// pass) the canonical residue is stored instead.  FUSE: the digit rows still
+// hold the inverse transform's intermediate; its columns are finished here
+// (inv_columns and InvDigit's factor), which saves a launch and is done again by
+// every workgroup of a column, so only in small launches.  Targets vary fastest after
 // the column block, so all targets of a column block run together and read
 // its digit rows from L2; with M a multiple of 8 a column block also stays on
 // one XCD (workgroups are dealt to the 8 XCDs round-robin).
-template <int LOGM, int T, class Map>
+template <int LOGM>
+__device__ __forceinline__ void finish_digits(double (&x)[16], uint32_t prime, double2 f,
+                                              const PrimeK* __restrict__ pk,
+                                              const double* __restrict__ twi) {
+  const double q = pk[prime].q, qinv = pk[prime].qinv;
+  inv_columns<LOGM>(x, twi + ((size_t)prime << (12 + LOGM)), q, qinv);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) x[v] = red_bal(mm_shoup(x[v], f.x, f.y, q), q, qinv);
+}
+
+template <int LOGM, int T, bool FUSE, class Map>
 __global__ __launch_bounds__(kThreads) void k_bconv_outer(Map map, uint32_t log_n,
                                                           const PrimeK* __restrict__ pk,
-                                                          const double* __restrict__ twf) {
+                                                          const double* __restrict__ twf,
+                                                          const double* __restrict__ twi) {
   constexpr int M = 1 << LOGM, C = 16 / M;
   const uint32_t g = blockIdx.z, t0 = blockIdx.y * T;
   const uint32_t nt = map.targets(g);
@@ -317,6 +336,7 @@ __global__ __launch_bounds__(kThreads) void k_bconv_outer(Map map, uint32_t log_
     for (int j = 0; j < C; ++j)
 #pragma unroll
       for (int m = 0; m < M; ++m) x[j * M + m] = da[kThreads * j + kBlock * m];
+    if constexpr (FUSE) finish_digits<LOGM>(x, map.src_prime(g, ac), map.factor(g, ac), pk, twi);
 #pragma unroll
     for (int i = 0; i < T; ++i) {
       const double q = pk[prime[i]].q;
@@ -379,6 +399,9 @@ struct ModupMap {
   const double2* mu_hat;
   uint32_t level, L, alpha, dnum_l, n;
   const int8_t* mu_bytes;  // matrix-core operands (LevelTables::mu_bytes), or null
+  const double2* f;        // InvDigit's factors of the digit rows (mu_inv_n)
+  __device__ uint32_t src_prime(uint32_t g, uint32_t a) const { return lo(g) + a; }
+  __device__ double2 factor(uint32_t g, uint32_t a) const { return f[lo(g) + a]; }
   __device__ uint32_t lo(uint32_t g) const { return (g % dnum_l) * alpha; }
   __device__ uint32_t aj(uint32_t g) const { return min(alpha, level - lo(g)); }
   __device__ uint32_t targets(uint32_t g) const { return level + alpha - aj(g); }
@@ -409,6 +432,10 @@ struct ModdownMap {
   const double2* md_hat;
   uint32_t level, alpha, n;
   const int8_t* md_bytes;  // matrix-core operands (LevelTables::md_bytes), or null
+  const double2* f;        // md_inv_n
+  uint32_t L;
+  __device__ uint32_t src_prime(uint32_t, uint32_t a) const { return L + a; }
+  __device__ double2 factor(uint32_t, uint32_t a) const { return f[a]; }
   __device__ uint32_t aj(uint32_t) const { return alpha; }
   __device__ uint32_t targets(uint32_t) const { return level; }
   __device__ uint32_t row(uint32_t, uint32_t t) const { return t; }
@@ -433,6 +460,10 @@ struct ModdownRescaleMap {
   const double2* mr_hat;
   uint32_t level, E, alpha, rows, n;  // alpha = number of digits (special primes + 1)
   const int8_t* mr_bytes;  // matrix-core operands of digits 0..7 (LevelTables::mr_bytes), or null
+  const double2* f;        // mr_inv_n
+  uint32_t L;
+  __device__ uint32_t src_prime(uint32_t, uint32_t a) const { return a ? L + a - 1 : level - 1; }
+  __device__ double2 factor(uint32_t, uint32_t a) const { return f[a]; }
   __device__ uint32_t aj(uint32_t) const { return alpha; }
   __device__ uint32_t targets(uint32_t) const { return rows; }
   __device__ uint32_t row(uint32_t, uint32_t t) const { return t; }
@@ -455,7 +486,10 @@ struct RescaleMap {
   uint64_t* w;
   const double2* one;  // {1, 1/q_i}
   uint32_t last, rows, n;
+  const double2* f;  // rs_ninv
   static constexpr uint32_t alpha = 1;
+  __device__ uint32_t src_prime(uint32_t, uint32_t) const { return last; }
+  __device__ double2 factor(uint32_t, uint32_t) const { return f[0]; }
   __device__ uint32_t aj(uint32_t) const { return 1; }
   __device__ uint32_t targets(uint32_t) const { return rows; }
   __device__ uint32_t row(uint32_t, uint32_t t) const { return t; }
@@ -493,9 +527,11 @@ __device__ __forceinline__ uint64_t bal_bytes(double x) {
 // of the outer pass, which then runs in registers as in k_bconv_outer.
 // The quads of a column share one load of the digits; blockIdx.y deals them out
 // where one workgroup per column and group would leave the chip idle.
-template <int LOGM, class Map, bool NINTH>
+// FUSE as in k_bconv_outer: a lane holds whole columns of its two sources.
+template <int LOGM, class Map, bool NINTH, bool FUSE>
 __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restrict__ pk,
-                                           const double* __restrict__ twf) {
+                                           const double* __restrict__ twf,
+                                           const double* __restrict__ twi) {
   constexpr uint32_t n = kBlock << LOGM;
   constexpr int M = 1 << LOGM, C = 16 / M;
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -520,12 +556,36 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
     const double* r0 = dig + (size_t)min(a0, aj - 1) * n + c;
     const double* r1 = dig + (size_t)min(a1, aj - 1) * n + c;
     const uint64_t k0 = a0 < aj ? ~0ull : 0ull, k1 = a1 < aj ? ~0ull : 0ull;
+    if constexpr (FUSE) {
+      double x[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const uint64_t p0 = bal_bytes(r0[at(v)]) & k0, p1 = bal_bytes(r1[at(v)]) & k1;
-      b[v] = v4i{(int)(uint32_t)p0, (int)(uint32_t)(p0 >> 32), (int)(uint32_t)p1,
-                 (int)(uint32_t)(p1 >> 32)};
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t a = min(h ? a1 : a0, aj - 1);
+        const double* r = h ? r1 : r0;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) x[v] = r[at(v)];
+        finish_digits<LOGM>(x, map.src_prime(g, a), map.factor(g, a), pk, twi);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const uint64_t p = bal_bytes(x[v]) & (h ? k1 : k0);
+          b[v][2 * h] = (int)(uint32_t)p;
+          b[v][2 * h + 1] = (int)(uint32_t)(p >> 32);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint64_t p0 = bal_bytes(r0[at(v)]) & k0, p1 = bal_bytes(r1[at(v)]) & k1;
+        b[v] = v4i{(int)(uint32_t)p0, (int)(uint32_t)(p0 >> 32), (int)(uint32_t)p1,
+                   (int)(uint32_t)(p1 >> 32)};
+      }
     }
+  }
+  double x8[16];  // the ninth source's digits
+  if constexpr (NINTH && FUSE) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x8[v] = d8[at(v)];
+    finish_digits<LOGM>(x8, map.src_prime(g, 8), map.factor(g, 8), pk, twi);
   }
   for (uint32_t q0 = 4 * blockIdx.y; q0 < nt; q0 += 4 * gridDim.y) {
     // A operands: product row col = target q0 + col / 4, digit tau = col % 4
@@ -558,7 +618,7 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
       const double cq = __builtin_rint(__builtin_fma(hi, k32, lo * qinv));
       double r = __builtin_fma(-cq, q, hi * 4294967296.0) + lo;
       if constexpr (NINTH)  // |r| < 1.2 q before the reduction, 0.5 q without it
-        r = red_bal(r + mm_shoup(d8[at(v)], h8.x, h8.y, q), q, qinv);
+        r = red_bal(r + mm_shoup(FUSE ? x8[v] : d8[at(v)], h8.x, h8.y, q), q, qinv);
       x[v] = r;
       // consume each pair of products here: otherwise the combination sinks
       // below the branch on tt and all 32 products (128 registers of
@@ -596,16 +656,18 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
 
 // Three waves per SIMD fit without spilling; the ninth-digit variant keeps
 // two (its extra loads would spill at three).
-template <int LOGM, class Map>
+template <int LOGM, bool FUSE, class Map>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_bconv_mfma(
-    Map map, const PrimeK* __restrict__ pk, const double* __restrict__ twf) {
-  bconv_mfma<LOGM, Map, false>(map, pk, twf);
+    Map map, const PrimeK* __restrict__ pk, const double* __restrict__ twf,
+    const double* __restrict__ twi) {
+  bconv_mfma<LOGM, Map, false, FUSE>(map, pk, twf, twi);
 }
 
-template <int LOGM, class Map>
+template <int LOGM, bool FUSE, class Map>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_bconv_mfma9(
-    Map map, const PrimeK* __restrict__ pk, const double* __restrict__ twf) {
-  bconv_mfma<LOGM, Map, true>(map, pk, twf);
+    Map map, const PrimeK* __restrict__ pk, const double* __restrict__ twf,
+    const double* __restrict__ twi) {
+  bconv_mfma<LOGM, Map, true, FUSE>(map, pk, twf, twi);
 }
 
 // ------------------------------------------------------------- inner pass
@@ -1003,8 +1065,8 @@ hipError_t launch_fwd_inner(const Context* c, const RowSel& rs, uint32_t batch, 
 // Inverse transform: inner pass (reading through Ld), then the outer pass; St
 // is the final store of whichever pass is last.
 template <class Ld, class St>
-hipError_t launch_inverse(const Context* c, const RowSel& rs, uint32_t batch, uint32_t limbs,
-                          const Ld& ld, const St& st, hipStream_t s) {
+hipError_t launch_inv_first(const Context* c, const RowSel& rs, uint32_t batch, uint32_t limbs,
+                            const Ld& ld, const St& st, hipStream_t s) {
   const dim3 grid(c->n / kBlock, batch, limbs), blk(kThreads);
   if (c->log_n == 12)
     k_inv_inner<true, Ld, St><<<grid, blk, 0, s>>>(rs, c->log_n, c->d_pk, c->d_tw_inv,
@@ -1012,7 +1074,12 @@ hipError_t launch_inverse(const Context* c, const RowSel& rs, uint32_t batch, ui
   else
     k_inv_inner<false, Ld, St><<<grid, blk, 0, s>>>(rs, c->log_n, c->d_pk, c->d_tw_inv,
                                                      c->d_tw3_inv, ld, st);
-  hipError_t e = hipGetLastError();
+  return hipGetLastError();
+}
+template <class Ld, class St>
+hipError_t launch_inverse(const Context* c, const RowSel& rs, uint32_t batch, uint32_t limbs,
+                          const Ld& ld, const St& st, hipStream_t s) {
+  const hipError_t e = launch_inv_first(c, rs, batch, limbs, ld, st, s);
   if (e != hipSuccess) return e;
   return launch_inv_outer(c, rs, batch, limbs, st, s);
 }
@@ -1049,23 +1116,52 @@ constexpr uint32_t kBconvFill = 768;
 // N = 2^12: 49 / 199 against 59 / 235, N = 2^15: 95 / 1339 against 107 / 1452.
 constexpr uint32_t kMfmaMinDigit = 4;
 
+template <class Map>
+bool on_matrix_cores(const Map& map) {
+  if constexpr (kMfmaMap<Map>) return mfma_bytes(map) && map.alpha >= kMfmaMinDigit;
+  return false;
+}
+
+// Whether a conversion finishes its digits' inverse transform itself, repeating
+// the columns in every workgroup that reads them: where its launch leaves the chip
+// room anyway, one launch and one trip through memory less.  One rotation at N =
+// 2^13, alpha = 1: 51 -> 40 us, N = 2^16, 24 limbs: 139 -> 130 us, two 244 -> 226
+// us; post-SSM at N = 2^14: 81 -> 69 us.  With the chip full (30 rotations) the
+// matrix-core kernel loses what the column pass saves.  (N = 4096 has no outer
+// pass.)
+template <class Map>
+bool fuse_digits(const Context* c, const Map& map, uint32_t targets, uint32_t groups) {
+  const uint32_t M = c->n / kBlock;
+  if (M == 1) return false;
+  return on_matrix_cores(map) ? 4 * M * groups * 2 <= kBconvFill
+                              : M * ((targets + 2) / 3) * groups < kBconvFill;
+}
+
 template <int LOGM, class Map>
 hipError_t launch_bconv_logm(const Context* c, const Map& map, uint32_t targets, uint32_t groups,
                              hipStream_t s) {
   constexpr uint32_t M = 1u << LOGM;
-  const double* tw = c->d_tw_fwd;
+  constexpr bool CAN = LOGM > 0;
+  const double *tw = c->d_tw_fwd, *ti = c->d_tw_inv;
+  const bool fuse = fuse_digits(c, map, targets, groups);
   if constexpr (kMfmaMap<Map>) {
-    if (mfma_bytes(map) && map.alpha >= kMfmaMinDigit) {
+    if (on_matrix_cores(map)) {
       const uint32_t quads = (targets + 3) / 4, cols = 4 * M * groups;
       const uint32_t split = std::min(quads, std::max(1u, kBconvFill / cols));
       const dim3 grid(4 * M, split, groups);
       if constexpr (std::is_same_v<Map, ModdownRescaleMap>) {
         if (map.alpha > 8) {  // q_{l-1} and eight special primes
-          k_bconv_mfma9<LOGM, Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, tw);
+          if (fuse)
+            k_bconv_mfma9<LOGM, CAN, Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, tw, ti);
+          else
+            k_bconv_mfma9<LOGM, false, Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, tw, ti);
           return hipGetLastError();
         }
       }
-      k_bconv_mfma<LOGM, Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, tw);
+      if (fuse)
+        k_bconv_mfma<LOGM, CAN, Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, tw, ti);
+      else
+        k_bconv_mfma<LOGM, false, Map><<<grid, kThreads, 0, s>>>(map, c->d_pk, tw, ti);
       return hipGetLastError();
     }
   }
@@ -1074,17 +1170,26 @@ hipError_t launch_bconv_logm(const Context* c, const Map& map, uint32_t targets,
   // N = 2^15, alpha = 3: 73 -> 66 us)
   if (M * ((targets + 2) / 3) * groups >= kBconvFill) {
     const dim3 grid(M, (targets + 2) / 3, groups);
-    k_bconv_outer<LOGM, 3, Map><<<grid, kThreads, 0, s>>>(map, c->log_n, c->d_pk, tw);
+    k_bconv_outer<LOGM, 3, false, Map><<<grid, kThreads, 0, s>>>(map, c->log_n, c->d_pk, tw, ti);
   } else {
     const dim3 grid(M, targets, groups);
-    k_bconv_outer<LOGM, 1, Map><<<grid, kThreads, 0, s>>>(map, c->log_n, c->d_pk, tw);
+    k_bconv_outer<LOGM, 1, CAN, Map><<<grid, kThreads, 0, s>>>(map, c->log_n, c->d_pk, tw, ti);
   }
   return hipGetLastError();
 }
 
-template <class Map>
-hipError_t launch_bconv_outer(const Context* c, const Map& map, uint32_t targets, uint32_t groups,
-                              hipStream_t s) {
+// Inverse transform of the rows rs selects (read through ld) to the centred
+// digits of `map`, and their conversion fused with the targets' first forward
+// pass.
+template <class Ld, class Map>
+hipError_t launch_convert(const Context* c, const RowSel& rs, uint32_t batch, uint32_t limbs,
+                          const Ld& ld, const Map& map, uint32_t targets, uint32_t groups,
+                          hipStream_t s) {
+  const InvDigit st{map.f};
+  hipError_t e = launch_inv_first(c, rs, batch, limbs, ld, st, s);
+  if (e == hipSuccess && !fuse_digits(c, map, targets, groups))
+    e = launch_inv_outer(c, rs, batch, limbs, st, s);
+  if (e != hipSuccess) return e;
   switch (c->log_n) {
     case 12: return launch_bconv_logm<0>(c, map, targets, groups, s);
     case 13: return launch_bconv_logm<1>(c, map, targets, groups, s);
@@ -1097,33 +1202,32 @@ hipError_t launch_bconv_outer(const Context* c, const Map& map, uint32_t targets
 
 }  // namespace
 
-// Inverse transform of the first `level` rows of each key-switch source into
-// cc[s][level][N] (out of place: the first pass reads the sources directly),
-// stored as the centred ModUp digits [N^-1 (Q_D/q_i)^-1 x]_{q_i} (fp64);
-// f = LevelTables::mu_inv_n.
-hipError_t launch_ntt_inv_sources(const Context* c, const KsTable& tab, uint32_t nsrc,
-                                  uint64_t* cc, uint32_t level, const double2* f, hipStream_t s) {
-  RowSel rs{cc, (size_t)level * c->n, (size_t)c->n, 0, level, 0, 0, 0, 0};
-  return launch_inverse(c, rs, nsrc, level, LoadSources{tab}, InvDigit{f}, s);
+// ModUp of every key-switch source: inverse transform of its first `level` rows
+// into cc[s][level][N] (out of place: the first pass reads the sources
+// directly) to the centred digits [N^-1 (Q_D/q_i)^-1 x]_{q_i} (fp64), and their
+// conversion fused with the first forward pass of the extended rows (own-digit
+// rows are not written).
+hipError_t launch_modup(const Context* c, const LevelTables& T, const KsTable& tab, uint32_t nsrc,
+                        uint64_t* cc, uint64_t* ext, uint32_t level, hipStream_t s) {
+  const RowSel rs{cc, (size_t)level * c->n, (size_t)c->n, 0, level, 0, 0, 0, 0};
+  const uint32_t dnum_l = (level + c->alpha - 1) / c->alpha;
+  const uint32_t aj_min = level - (dnum_l - 1) * c->alpha;
+  const ModupMap map{reinterpret_cast<const double*>(cc), ext, T.mu_hat, level, c->L, c->alpha,
+                     dnum_l, c->n, T.mu_bytes, T.mu_inv_n};
+  return launch_convert(c, rs, nsrc, level, LoadSources{tab}, map, level + c->alpha - aj_min,
+                        nsrc * dnum_l, s);
 }
 
-// Rescale, step 1: inverse transform of nrows single rows under prime
-// `last`, row r read from tab.src_in[r], stored into v[r][N] as the centred
-// coefficients [N^-1 x]_{q_last} (fp64; ninv = {N^-1 mod q_last, /q_last}).
-hipError_t launch_ntt_inv_rescale_last(const Context* c, const KsTable& tab, uint32_t nrows,
-                                       uint64_t* v, uint32_t last, const double2* ninv,
-                                       hipStream_t s) {
-  RowSel rs{v, (size_t)c->n, (size_t)c->n, last, 1, 0, 0, 0, 0};
-  return launch_inverse(c, rs, nrows, 1, LoadSources{tab}, InvDigit{ninv}, s);
-}
-
-// Rescale, step 2: each centred last limb lifted to rows 0 .. rows-1 (a
-// conversion with one digit and weight 1) fused with their first forward
-// pass, into w[g][last][N].
-hipError_t launch_rescale_outer(const Context* c, const uint64_t* v, uint64_t* w, uint32_t groups,
-                                uint32_t last, uint32_t rows, const double2* one, hipStream_t s) {
-  const RescaleMap map{reinterpret_cast<const double*>(v), w, one, last, rows, c->n};
-  return launch_bconv_outer(c, map, rows, groups, s);
+// Rescale, steps 1 and 2: inverse transform of nrows single rows under prime
+// `last`, row r read from tab.src_in[r], into v[r][N] as centred coefficients
+// [N^-1 x]_{q_last} (fp64), and their lift to rows 0 .. rows-1 (a conversion with
+// one digit and weight 1) fused with the first forward pass, into w[r][last][N].
+hipError_t launch_rescale_lift(const Context* c, const LevelTables& T, const KsTable& tab,
+                               uint32_t nrows, uint64_t* v, uint64_t* w, uint32_t last,
+                               uint32_t rows, hipStream_t s) {
+  const RowSel rs{v, (size_t)c->n, (size_t)c->n, last, 1, 0, 0, 0, 0};
+  const RescaleMap map{reinterpret_cast<const double*>(v), w, T.one, last, rows, c->n, T.rs_ninv};
+  return launch_convert(c, rs, nrows, 1, LoadSources{tab}, map, rows, nrows, s);
 }
 
 // Rescale, step 3: second forward pass of w with the combine
@@ -1135,51 +1239,37 @@ hipError_t launch_ntt_fwd_rs_combine(const Context* c, uint64_t* w, uint32_t cou
   return launch_fwd_inner(c, rs, 2 * count, rows, RsCombine{tab, qlinv}, s);
 }
 
-// Inverse transform of the rows rs selects (in place), stored as centred
-// digits [N^-1 f_i x]_{q_i} (fp64), f per limb.
-hipError_t launch_ntt_inv_digits(const Context* c, const RowSel& rs, uint32_t batch,
-                                 uint32_t limbs, const double2* f, hipStream_t s) {
-  return launch_inverse(c, rs, batch, limbs, LoadRow{}, InvDigit{f}, s);
+// ModDown of the special-prime rows of acc: inverse transform in place to
+// centred digits, conversion fused with the first forward pass of y.
+hipError_t launch_moddown(const Context* c, const LevelTables& T, uint64_t* acc, uint64_t* y,
+                          uint32_t njobs, uint32_t level, hipStream_t s) {
+  const size_t n = c->n;
+  const RowSel rs{acc + level * n, (level + c->alpha) * n, n, c->L, c->alpha, 0, 0, 0, 0};
+  const ModdownMap map{acc, y, T.md_hat, level, c->alpha, c->n, T.md_bytes, T.md_inv_n, c->L};
+  return launch_convert(c, rs, 2 * njobs, c->alpha, LoadRow{}, map, level, 2 * njobs, s);
 }
 
-// ModUp of every source (digits from launch_ntt_inv_sources) fused with the
-// first forward pass of the extended rows (own-digit rows are not written).
-hipError_t launch_modup_outer(const Context* c, const LevelTables& T, const uint64_t* cc,
-                              uint64_t* ext, uint32_t nsrc, uint32_t level, hipStream_t s) {
-  const uint32_t dnum_l = (level + c->alpha - 1) / c->alpha;
-  const uint32_t aj_min = level - (dnum_l - 1) * c->alpha;
-  const ModupMap map{reinterpret_cast<const double*>(cc), ext, T.mu_hat, level, c->L, c->alpha,
-                     dnum_l, c->n, T.mu_bytes};
-  return launch_bconv_outer(c, map, level + c->alpha - aj_min, nsrc * dnum_l, s);
-}
-
-// ModDown conversion of the special-prime rows of acc (digits from
-// launch_ntt_inv_digits) fused with the first forward pass of y.
-hipError_t launch_moddown_outer(const Context* c, const LevelTables& T, const uint64_t* acc,
-                                uint64_t* y, uint32_t njobs, uint32_t level, hipStream_t s) {
-  const ModdownMap map{acc, y, T.md_hat, level, c->alpha, c->n, T.md_bytes};
-  return launch_bconv_outer(c, map, level, 2 * njobs, s);
-}
-
-// Second forward pass of rows whose first pass has run (launch_modup_outer).
+// Second forward pass of rows whose first pass has run (launch_modup, the encoder's lift).
 hipError_t launch_ntt_fwd_inner_rows(const Context* c, const RowSel& rs, uint32_t batch,
                                      uint32_t limbs, hipStream_t s) {
   return launch_fwd_inner(c, rs, batch, limbs, StoreResidues{}, s);
 }
 
-// ModDown merged with the rescale: conversion of the alpha + 1 digit rows of
-// acc (launch_ntt_inv_digits with mr_inv_n) to rows 0 .. rows-1, fused with
-// the first forward pass of y[2*njobs][level-1][N].
-hipError_t launch_moddown_rescale_outer(const Context* c, const LevelTables& T,
-                                        const uint64_t* acc, uint64_t* y, uint32_t njobs,
-                                        uint32_t level, uint32_t rows, hipStream_t s) {
-  const ModdownRescaleMap map{acc, y, T.mr_hat, level, level + c->alpha, c->alpha + 1, rows,
-                              c->n, T.mr_bytes};
-  return launch_bconv_outer(c, map, rows, 2 * njobs, s);
+// ModDown merged with the rescale: rows q_{level-1}, p_0 .. p_{alpha-1} (adjacent
+// in acc) to the centred digits of M = P q_{level-1}, their conversion to rows 0
+// .. rows-1 fused with the first forward pass of y[2*njobs][level-1][N].
+hipError_t launch_moddown_rescale(const Context* c, const LevelTables& T, uint64_t* acc,
+                                  uint64_t* y, uint32_t njobs, uint32_t level, uint32_t rows,
+                                  hipStream_t s) {
+  const size_t n = c->n;
+  const RowSel rs{acc + (level - 1) * n, (level + c->alpha) * n, n, level - 1, 1, c->L, 0, 0, 0};
+  const ModdownRescaleMap map{acc,  y,    T.mr_hat,   level,      level + c->alpha, c->alpha + 1,
+                              rows, c->n, T.mr_bytes, T.mr_inv_n, c->L};
+  return launch_convert(c, rs, 2 * njobs, c->alpha + 1, LoadRow{}, map, rows, 2 * njobs, s);
 }
 
 // Second forward pass of the ModDown conversions y[2*njobs][ystride][N]
-// (first pass: launch_moddown_outer or launch_moddown_rescale_outer) with the
+// (first pass: launch_moddown or launch_moddown_rescale) with the
 // key-switch combine as the epilogue; writes rows 0 .. rows-1 of the jobs'
 // outputs.  qlinv: null, or q_{level-1}^-1 per row (merged rescale).
 hipError_t launch_ntt_fwd_ks_combine(const Context* c, uint64_t* y, uint32_t njobs,

@@ -271,8 +271,7 @@ int key_switch_batch(Context* c, uint32_t level, const std::vector<KsSource>& sr
   // iNTT of the sources, stored as centred ModUp digits; ModUp fused with the
   // first forward pass of the extended rows; second pass (own-digit rows are
   // never written: the inner product reads them from the source)
-  HIPCK(launch_ntt_inv_sources(c, tab, ns, S.cc, level, T->mu_inv_n, s));
-  HIPCK(launch_modup_outer(c, *T, S.cc, S.ext, ns, level, s));
+  HIPCK(launch_modup(c, *T, tab, ns, S.cc, S.ext, level, s));
   RowSel rs{S.ext, (size_t)E * n, n, 0, level, c->L, c->alpha, level, dnum_l};
   HIPCK(launch_ntt_fwd_inner_rows(c, rs, ns * dnum_l, E, s));
   // jobs
@@ -324,19 +323,14 @@ int key_switch_batch(Context* c, uint32_t level, const std::vector<KsSource>& sr
       // rows q_{level-1}, p_0 .. p_{alpha-1} (adjacent in acc): iNTT to the
       // centred digits of M = P q_{level-1}; conversion to the kept rows fused
       // with the first forward pass; combine times q_{level-1}^-1
-      const RowSel rp{S.acc + (size_t)(level - 1) * n, (size_t)E * n, n, level - 1, 1, c->L,
-                      0, 0, 0};
-      HIPCK(launch_ntt_inv_digits(c, rp, 2 * nj, c->alpha + 1, T->mr_inv_n, s));
-      HIPCK(launch_moddown_rescale_outer(c, *T, S.acc, S.y, nj, level, rescale_rows, s));
+      HIPCK(launch_moddown_rescale(c, *T, S.acc, S.y, nj, level, rescale_rows, s));
       HIPCK(launch_ntt_fwd_ks_combine(c, S.y, nj, level, rescale_rows, level - 1, t, S.acc,
                                       T->md_pinv, T->rs_inv, s));
       continue;
     }
     // special-prime rows: iNTT to centred ModDown digits, conversion fused
     // with the first forward pass of y, second pass ending in the combine
-    const RowSel rp{S.acc + (size_t)level * n, (size_t)E * n, n, c->L, c->alpha, 0, 0, 0, 0};
-    HIPCK(launch_ntt_inv_digits(c, rp, 2 * nj, c->alpha, T->md_inv_n, s));
-    HIPCK(launch_moddown_outer(c, *T, S.acc, S.y, nj, level, s));
+    HIPCK(launch_moddown(c, *T, S.acc, S.y, nj, level, s));
     HIPCK(launch_ntt_fwd_ks_combine(c, S.y, nj, level, level, level, t, S.acc, T->md_pinv,
                                     nullptr, s));
   }
@@ -360,9 +354,7 @@ int op_moddown_many(Context* c, uint32_t count, uint64_t* ext, uint64_t* const* 
     uint64_t* acc = ext + (size_t)j0 * 2 * E * n;
     KsTable t{};
     for (uint32_t j = 0; j < nj; ++j) t.out[j] = outs[j0 + j];
-    const RowSel rp{acc + (size_t)level * n, E * n, n, c->L, c->alpha, 0, 0, 0, 0};
-    HIPCK(launch_ntt_inv_digits(c, rp, 2 * nj, c->alpha, T->md_inv_n, s));
-    HIPCK(launch_moddown_outer(c, *T, acc, S.y, nj, level, s));
+    HIPCK(launch_moddown(c, *T, acc, S.y, nj, level, s));
     HIPCK(launch_ntt_fwd_ks_combine(c, S.y, nj, level, level, level, t, acc, T->md_pinv,
                                     nullptr, s));
   }
@@ -524,8 +516,7 @@ int op_rescale_add_many(Context* c, uint32_t count, const uint64_t* const* ins,
     }
     // last limbs to centred coefficients (fp64), lifted to the kept rows
     // inside the first forward pass, combined in the second pass's epilogue
-    HIPCK(launch_ntt_inv_rescale_last(c, tab, 2 * m, v, last, T->rs_ninv, s));
-    HIPCK(launch_rescale_outer(c, v, w, 2 * m, last, out_rows, T->one, s));
+    HIPCK(launch_rescale_lift(c, *T, tab, 2 * m, v, w, last, out_rows, s));
     HIPCK(launch_ntt_fwd_rs_combine(c, w, m, last, out_rows, rt, T->rs_inv, s));
   }
   return FESC_OK;

@@ -108,27 +108,21 @@ struct KsTable {
 
 // ntt.hip: transforms of the key-switch pipeline (inverse transforms store
 // centred conversion digits; conversions are fused with the first forward pass)
-hipError_t launch_ntt_inv_sources(const Context* c, const KsTable& tab, uint32_t nsrc,
-                                  uint64_t* cc, uint32_t level, const double2* f, hipStream_t s);
-hipError_t launch_ntt_inv_rescale_last(const Context* c, const KsTable& tab, uint32_t nrows,
-                                       uint64_t* v, uint32_t last, const double2* ninv,
-                                       hipStream_t s);
-hipError_t launch_rescale_outer(const Context* c, const uint64_t* v, uint64_t* w, uint32_t groups,
-                                uint32_t last, uint32_t rows, const double2* one, hipStream_t s);
+hipError_t launch_modup(const Context* c, const LevelTables& T, const KsTable& tab, uint32_t nsrc,
+                        uint64_t* cc, uint64_t* ext, uint32_t level, hipStream_t s);
+hipError_t launch_rescale_lift(const Context* c, const LevelTables& T, const KsTable& tab,
+                               uint32_t nrows, uint64_t* v, uint64_t* w, uint32_t last,
+                               uint32_t rows, hipStream_t s);
 hipError_t launch_ntt_fwd_rs_combine(const Context* c, uint64_t* w, uint32_t count, uint32_t last,
                                      uint32_t rows, const RsTable& tab, const double2* qlinv,
                                      hipStream_t s);
-hipError_t launch_ntt_inv_digits(const Context* c, const RowSel& rs, uint32_t batch,
-                                 uint32_t limbs, const double2* f, hipStream_t s);
-hipError_t launch_modup_outer(const Context* c, const LevelTables& T, const uint64_t* cc,
-                              uint64_t* ext, uint32_t nsrc, uint32_t level, hipStream_t s);
-hipError_t launch_moddown_outer(const Context* c, const LevelTables& T, const uint64_t* acc,
-                                uint64_t* y, uint32_t njobs, uint32_t level, hipStream_t s);
+hipError_t launch_moddown(const Context* c, const LevelTables& T, uint64_t* acc, uint64_t* y,
+                          uint32_t njobs, uint32_t level, hipStream_t s);
 hipError_t launch_ntt_fwd_inner_rows(const Context* c, const RowSel& rs, uint32_t batch,
                                      uint32_t limbs, hipStream_t s);
-hipError_t launch_moddown_rescale_outer(const Context* c, const LevelTables& T,
-                                        const uint64_t* acc, uint64_t* y, uint32_t njobs,
-                                        uint32_t level, uint32_t rows, hipStream_t s);
+hipError_t launch_moddown_rescale(const Context* c, const LevelTables& T, uint64_t* acc,
+                                  uint64_t* y, uint32_t njobs, uint32_t level, uint32_t rows,
+                                  hipStream_t s);
 hipError_t launch_ntt_fwd_ks_combine(const Context* c, uint64_t* y, uint32_t njobs,
                                      uint32_t level, uint32_t rows, uint32_t ystride,
                                      const KsTable& tab, const uint64_t* acc,
