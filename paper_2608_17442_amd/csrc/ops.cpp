@@ -271,9 +271,13 @@ int key_switch_batch(Context* c, uint32_t level, const std::vector<KsSource>& sr
   // iNTT of the sources, stored as centred ModUp digits; ModUp fused with the
   // first forward pass of the extended rows; second pass (own-digit rows are
   // never written: the inner product reads them from the source)
-  HIPCK(launch_modup(c, *T, tab, ns, S.cc, S.ext, level, s));
-  RowSel rs{S.ext, (size_t)E * n, n, 0, level, c->L, c->alpha, level, dnum_l};
-  HIPCK(launch_ntt_fwd_inner_rows(c, rs, ns * dnum_l, E, s));
+  if (small_modup_fits(c, ns, level)) {
+    HIPCK(launch_small_modup(c, *T, tab, ns, S.ext, level, s));
+  } else {
+    HIPCK(launch_modup(c, *T, tab, ns, S.cc, S.ext, level, s));
+    RowSel rs{S.ext, (size_t)E * n, n, 0, level, c->L, c->alpha, level, dnum_l};
+    HIPCK(launch_ntt_fwd_inner_rows(c, rs, ns * dnum_l, E, s));
+  }
   // jobs
   // jobs ordered by (key, Galois element): each group of kMaxBatch jobs then
   // holds few distinct keys, and the inner product reads each key once
@@ -319,6 +323,10 @@ int key_switch_batch(Context* c, uint32_t level, const std::vector<KsSource>& sr
       continue;
     }
     HIPCK(k_ip_launch(c, t, nkeys, S.ext, S.acc, level, T->md_pinv, s));
+    if (small_moddown_fits(c, t, nj, rescale_rows ? rescale_rows : level)) {
+      HIPCK(launch_small_moddown(c, *T, t, nj, S.acc, level, rescale_rows, s));
+      continue;
+    }
     if (rescale_rows) {
       // rows q_{level-1}, p_0 .. p_{alpha-1} (adjacent in acc): iNTT to the
       // centred digits of M = P q_{level-1}; conversion to the kept rows fused
@@ -513,6 +521,10 @@ int op_rescale_add_many(Context* c, uint32_t count, const uint64_t* const* ins,
       rt.in[b] = ins[b0 + b];
       rt.out[b] = outs[b0 + b];
       rt.add[b] = adds ? adds[b0 + b] : nullptr;
+    }
+    if (small_rescale_fits(c, rt, m, last, out_rows)) {
+      HIPCK(launch_small_rescale(c, *T, rt, m, last, out_rows, s));
+      continue;
     }
     // last limbs to centred coefficients (fp64), lifted to the kept rows
     // inside the first forward pass, combined in the second pass's epilogue

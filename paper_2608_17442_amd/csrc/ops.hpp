@@ -130,6 +130,21 @@ hipError_t launch_ntt_fwd_ks_combine(const Context* c, uint64_t* y, uint32_t njo
 hipError_t k_ip_launch(const Context* c, const KsTable& tab, uint32_t nkeys, const uint64_t* ext,
                        uint64_t* acc, uint32_t level, const double2* pinv, hipStream_t s);
 
+// ---------------------------------------------------------- small_ring.hip
+// The key switch and the rescale at N = 4096 in fewer launches; the *_fit(s)
+// functions say whether a batch may take them (same scratch regions, same residues).
+bool small_modup_fits(const Context* c, uint32_t nsrc, uint32_t level);
+hipError_t launch_small_modup(const Context* c, const LevelTables& T, const KsTable& tab,
+                              uint32_t nsrc, uint64_t* ext, uint32_t level, hipStream_t s);
+bool small_moddown_fits(const Context* c, const KsTable& t, uint32_t njobs, uint32_t rows);
+hipError_t launch_small_moddown(const Context* c, const LevelTables& T, const KsTable& tab,
+                                uint32_t njobs, const uint64_t* acc, uint32_t level,
+                                uint32_t rescale_rows, hipStream_t s);
+bool small_rescale_fits(const Context* c, const RsTable& t, uint32_t count, uint32_t last,
+                        uint32_t rows);
+hipError_t launch_small_rescale(const Context* c, const LevelTables& T, const RsTable& tab,
+                                uint32_t count, uint32_t last, uint32_t rows, hipStream_t s);
+
 // ------------------------------------------------------------------ ops.cpp
 const LevelTables* level_tables(Context* c, uint32_t level, int* err);
 

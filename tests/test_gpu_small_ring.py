@@ -1,0 +1,97 @@
+"""GPU parity of the fused key switch and rescale at N = 4096: digits of one to
+three primes, a last digit of one prime, seed-expanded and stored keys in one
+batch, product sources, batches on both sides of the sizes at which the general
+pipeline takes over, and outputs that overlap what the batch reads.  Bit-exact
+against the oracle on uniform residues."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import ckks as C
+from tests.gpu_helpers import first_mismatch, need_gpu, step, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+SEED = 23
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    need_gpu()
+
+
+def _residues(P, level, i):
+    return np.stack([synth.uniform_residues(SEED, f"c{t}", P.qs(level), P.n, i)
+                     for t in range(2)], axis=1)
+
+
+def _eq(dev, want, what):
+    got = to_host(dev).reshape(want.shape)
+    assert np.array_equal(got, want), f"{what}: {first_mismatch(got, want)}"
+
+
+# the limits: 14 | 15 sources of 8 x 9 extended rows in the ModUp, 5 | 6 jobs of 29
+# rows in the ModDown (alpha 3); up to 15 digits in groups of three for the
+# seed-expanded half; alpha 4 takes the general pipeline
+@pytest.mark.parametrize("bits,L,alpha,level,count", [
+    (50, 3, 1, 3, 1), (36, 3, 1, 2, 5), (50, 8, 1, 8, 14), (50, 8, 1, 8, 15), (45, 7, 2, 7, 1),
+    (50, 7, 3, 7, 2), (50, 6, 3, 5, 32), (50, 16, 1, 15, 3), (36, 29, 3, 29, 5),
+    (36, 29, 3, 29, 6), (50, 5, 4, 5, 2),
+])
+def test_small_ring(bits, L, alpha, level, count):
+    from paper_2608_17442_amd import fesc as F
+    P = C.params_small(12, bits, L, alpha)
+    ctx = F.Context(P.log_n, P.q, P.p)
+    s = synth.secret(SEED, P.n)
+    sk, s_dev = C.secret_key(P, s), torch.from_numpy(s).cuda()
+    steps = [3, -5]
+    g_seed, keys = P.galois_elt(-5), {}
+    step(f"keys L={L} alpha={alpha}")
+    w, e = synth.switch_key_seed_draws(SEED, P.ext(P.L), P.n, P.dnum, g_seed)
+    ctx.keygen_seeded(g_seed, s_dev, w, torch.from_numpy(e).cuda())
+    keys[g_seed] = C.keygen_seeded(P, sk, w, e, g_seed)
+    for g in (0, P.galois_elt(3)):
+        mods = P.ext(P.L)
+        keys[g] = np.stack([np.stack([synth.uniform_residues(SEED, f"k{g}{t}", mods, P.n, j)
+                                      for t in range(2)], axis=1) for j in range(P.dnum)])
+        ctx.key_load(g, to_dev(keys[g]))
+    kinds = min(count, 3)
+    cts = [_residues(P, level, i) for i in range(kinds)]
+    host = [cts[i % kinds] for i in range(count)]
+    dev = [to_dev(c).reshape(-1) for c in host]
+    pick = sorted({0, count // 2, count - 1})
+    r = [steps[i % 2] for i in range(count)]
+
+    def fresh(rows):
+        return [torch.zeros(rows * 2 * P.n, dtype=torch.int64, device="cuda") for _ in dev]
+
+    step(f"rotate count={count} level={level}")
+    outs = fresh(level)
+    ctx.rotate_batch(dev, r, outs, level)
+    for i in pick:
+        _eq(outs[i], C.rotate(P, host[i], r[i], keys), f"rotate {i}")
+    step("hoisted")
+    hoisted = [torch.zeros_like(dev[0]) for _ in steps]
+    ctx.rotate_hoisted(dev[0], steps, hoisted, level)
+    for o, want in zip(hoisted, C.rotate_hoisted(P, host[0], steps, keys)):
+        _eq(o, want, "hoisted")
+    step("products")
+    outs = fresh(level - 1)
+    ctx.mul_relin_rescale(dev, dev[::-1], outs, level)
+    for i in pick:
+        _eq(outs[i], C.mul_relin_rescale(P, host[i], host[count - 1 - i], keys[0]), f"merged {i}")
+    prod = torch.zeros_like(dev[0])
+    ctx.mul_relin(dev[0], dev[-1], prod, level)
+    _eq(prod, C.mul_relin(P, host[0], host[-1], keys[0]), "product")
+    step("rescale")
+    low = torch.zeros((level - 1) * 2 * P.n, dtype=torch.int64, device="cuda")
+    ctx.rescale(dev[0], low, level)
+    _eq(low, C.rescale(P, host[0]), "rescale")
+    step("in place: a square, a rotation, a rescale")
+    ctx.mul_relin(prod, prod, prod, level)
+    _eq(prod, C.mul_relin(P, *2 * [C.mul_relin(P, host[0], host[-1], keys[0])], keys[0]), "square")
+    ctx.rotate(dev[0], dev[0], level, r[0])
+    _eq(dev[0], C.rotate(P, host[0], r[0], keys), "rotation in place")
+    ctx.rescale(dev[0], dev[0], level)
+    want = C.rescale(P, C.rotate(P, host[0], r[0], keys))
+    _eq(dev[0][:want.size], want, "rescale in place")
