@@ -130,8 +130,8 @@ def _ptr(t, words: int = 0, what: str = "buffer", dtype=torch.int64):
         raise TypeError(f"{what}: expected a CUDA {dtype} tensor")
     if not t.is_contiguous():
         raise ValueError(f"{what}: tensor must be contiguous")
-    need = words * torch.empty((), dtype=dtype).element_size()
-    have = t.numel() * t.element_size()
+    need = words * dtype.itemsize
+    have = t.numel() * dtype.itemsize
     if have < need:
         raise ValueError(f"{what}: {have} bytes, the call reads or writes {need}")
     return t.data_ptr()
