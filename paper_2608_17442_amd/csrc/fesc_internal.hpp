@@ -150,8 +150,8 @@ struct Context {
   // representative in [-q/2, q/2]
   double* d_tw_fwd = nullptr;
   double* d_tw_inv = nullptr;
-  // the powers used by the radix-16 step on index bits 3..0 of the 4096-point
-  // inner NTT blocks, re-ordered [L+alpha][N/4096][15][256] (see ntt.hip)
+  // [L+alpha][N/4096][256]: each inner-pass thread's power, from which it generates
+  // the twiddles of index bits 3..0 (TwGen)
   double* d_tw3_fwd = nullptr;
   double* d_tw3_inv = nullptr;
   // device encoding: T[k] = exp(-i pi k / N) for k < 2N, and the inverse slot

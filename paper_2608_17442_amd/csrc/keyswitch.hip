@@ -1,6 +1,7 @@
 // Hybrid key switching (digit decomposition with special primes): the key
 // inner product.  The rest of the pipeline lives with the transforms
-// (ntt.hip), fused into their passes:
+// (ntt.hip; for small batches at N = 4096 steps 1 and 2, and step 4, are one
+// launch each, small_ring.hip), fused into their passes:
 //   1. inverse NTT of each source polynomial, reading the caller's rows
 //      directly; its last pass stores the centred ModUp digits
 //          x_a = [c_a * (Q_D/q_a)^-1]_{q_a} in (-q_a/2, q_a/2)  (fp64);
