@@ -504,7 +504,7 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
     const uint32_t tt = q0 + lg;
     const uint32_t trow = map.row(g, min(tt, nt - 1));
     const uint32_t prime = map.prime(trow);
-    const double q = pk[prime].q, qinv = pk[prime].qinv, k32 = 4294967296.0 * qinv;
+    const double q = pk[prime].q, qinv = pk[prime].qinv;
     double2 h8{0.0, 0.0};
     if constexpr (NINTH) h8 = map.hat(g, trow)[8];
     const v4i zero = {0, 0, 0, 0};
@@ -513,15 +513,16 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
     for (int v = 0; v < 16; ++v) {
       const v4i dl = __builtin_amdgcn_mfma_i32_16x16x64_i8(alo, b[v], zero, 0, 0, 0);
       const v4i dh = __builtin_amdgcn_mfma_i32_16x16x64_i8(ahi, b[v], zero, 0, 0, 0);
-      // R = hi 2^32 + lo exactly (|lo| < 2^45, |hi| < 2^37), each |Q_tau| <=
+      // R = hi + lo exactly (|lo| < 2^45, |hi| < 2^69), each |Q_tau| <=
       // 64 * 2^14 = 2^20, so digit pairs Q_t + 256 Q_t+1 still fit an int32
       // and are combined before the conversion to fp64; y = R - c q with
       // c = round(R / q), formed exactly (the fma's result is below 2^51)
       const double lo = __builtin_fma((double)(dl[2] + dl[3] * 256), 65536.0,
                                       (double)(dl[0] + dl[1] * 256));
-      const double hi = __builtin_fma((double)dh[2], 65536.0, (double)(dh[0] + dh[1] * 256));
-      const double cq = __builtin_rint(__builtin_fma(hi, k32, lo * qinv));
-      double r = __builtin_fma(-cq, q, hi * 4294967296.0) + lo;
+      const double hi = __builtin_fma((double)dh[2], 65536.0, (double)(dh[0] + dh[1] * 256)) *
+                        4294967296.0;
+      const double cq = __builtin_rint(__builtin_fma(hi, qinv, lo * qinv));
+      double r = __builtin_fma(-cq, q, hi) + lo;
       if constexpr (NINTH)  // |r| < 1.2 q before the reduction, 0.5 q without it
         r = red_bal(r + mm_shoup(FUSE ? x8[v] : d8[at(v)], h8.x, h8.y, q), q, qinv);
       x[v] = r;
