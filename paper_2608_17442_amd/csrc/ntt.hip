@@ -233,19 +233,18 @@ __global__ __launch_bounds__(kThreads) void k_bconv_outer(Map map, uint32_t log_
     for (int v = 0; v < 16; ++v) y[i][v] = 0.0;
   // |x_a| < 2^49 and hat_a < m: each Shoup product lies within 0.625 m, so
   // eight terms and a carried reduced sum stay below 2^53
-  for (uint32_t a = 0; a < map.alpha; ++a) {
-    const uint32_t ac = a < aj ? a : aj - 1;
-    const double* da = dig + (size_t)ac * n + c0;
+  for (uint32_t a = 0; a < aj; ++a) {
+    const double* da = dig + (size_t)a * n + c0;
     double x[16];
 #pragma unroll
     for (int j = 0; j < C; ++j)
 #pragma unroll
       for (int m = 0; m < M; ++m) x[j * M + m] = da[kThreads * j + kBlock * m];
-    if constexpr (FUSE) finish_digits<LOGM>(x, map.src_prime(g, ac), map.factor(g, ac), pk, twi);
+    if constexpr (FUSE) finish_digits<LOGM>(x, map.src_prime(g, a), map.factor(g, a), pk, twi);
 #pragma unroll
     for (int i = 0; i < T; ++i) {
       const double q = pk[prime[i]].q;
-      const double2 h = a < aj ? hat[i][ac] : double2{0.0, 0.0};
+      const double2 h = hat[i][a];
 #pragma unroll
       for (int v = 0; v < 16; ++v) y[i][v] += mm_shoup(x[v], h.x, h.y, q);
     }
