@@ -35,6 +35,7 @@
 
 #include "block4096.hpp"
 #include "butterfly.hpp"
+#include "conversion_rule.hpp"
 #include "fesc_internal.hpp"
 #include "ops.hpp"
 
@@ -935,12 +936,6 @@ __host__ inline const int8_t* mfma_bytes(const ModdownRescaleMap& m) {
   return m.alpha <= 9 ? m.mr_bytes : nullptr;  // at most one digit past the eight
 }
 
-// Workgroups that fill the chip once at the matrix-core conversion's three
-// waves per SIMD (256 CUs).  A batch of one key switch has far fewer
-// (column block, digit) pairs, so its quads of targets go to different
-// workgroups; each of those loads the digits again, from L2: one rotation at
-// N = 2^16, 24 limbs, alpha = 8: 151 -> 138 us.
-constexpr uint32_t kBconvFill = 768;
 // Digits of fewer primes leave most of the product's 64-deep sums empty and
 // cost less as Shoup products on the VALU.  Rotations, matrix cores against
 // VALU (one / 30 at a time, us): alpha = 3, N = 2^15: 68 / 534 against
@@ -955,19 +950,25 @@ bool on_matrix_cores(const Map& map) {
   return false;
 }
 
+template <class Map>
+uint32_t longest_digit(const Map& map) {
+  if constexpr (std::is_same_v<Map, ModupMap>) return std::min(map.alpha, map.level);
+  return map.alpha;
+}
+
 // Whether a conversion finishes its digits' inverse transform itself, repeating
-// the columns in every workgroup that reads them: where its launch leaves the chip
-// room anyway, one launch and one trip through memory less.  One rotation at N =
-// 2^13, alpha = 1: 51 -> 40 us, N = 2^16, 24 limbs: 139 -> 130 us, two 244 -> 226
-// us; post-SSM at N = 2^14: 81 -> 69 us.  With the chip full (30 rotations) the
-// matrix-core kernel loses what the column pass saves.  (N = 4096 has no outer
-// pass.)
+// the columns in every workgroup that reads them.  On the VALU: valu_conversion.
+// On the matrix cores a lane finishes two sources whatever the digit's length;
+// it pays while the launch leaves the chip room: one rotation at N = 2^16, 24
+// limbs, alpha = 8: 139 -> 130 us, two 244 -> 226 us, not with the chip full (30
+// rotations).  (N = 4096 has no outer pass.)
 template <class Map>
 bool fuse_digits(const Context* c, const Map& map, uint32_t targets, uint32_t groups) {
   const uint32_t M = c->n / kBlock;
   if (M == 1) return false;
-  return on_matrix_cores(map) ? 4 * M * groups * 2 <= kBconvFill
-                              : M * ((targets + 2) / 3) * groups < kBconvFill;
+  return on_matrix_cores(map)
+             ? 4 * M * groups * 2 <= kBconvFill
+             : valu_conversion(c->log_n - 12, longest_digit(map), targets, groups).fuse;
 }
 
 template <int LOGM, class Map>
@@ -979,6 +980,10 @@ hipError_t launch_bconv_logm(const Context* c, const Map& map, uint32_t targets,
   const bool fuse = fuse_digits(c, map, targets, groups);
   if constexpr (kMfmaMap<Map>) {
     if (on_matrix_cores(map)) {
+      // A batch of one key switch has far fewer (column block, digit) pairs than
+      // fill the chip, so its quads of targets go to different workgroups; each of
+      // those loads the digits again, from L2: one rotation at N = 2^16, 24 limbs,
+      // alpha = 8: 151 -> 138 us.
       const uint32_t quads = (targets + 3) / 4, cols = 4 * M * groups;
       const uint32_t split = std::min(quads, std::max(1u, kBconvFill / cols));
       const dim3 grid(4 * M, split, groups);
@@ -998,16 +1003,14 @@ hipError_t launch_bconv_logm(const Context* c, const Map& map, uint32_t targets,
       return hipGetLastError();
     }
   }
-  // VALU conversion: three targets share a load of the digits where that
-  // still fills the chip, else one target per workgroup (one rotation at
-  // N = 2^15, alpha = 3: 73 -> 66 us)
-  if (M * ((targets + 2) / 3) * groups >= kBconvFill) {
-    const dim3 grid(M, (targets + 2) / 3, groups);
+  const ValuConversion v = valu_conversion(LOGM, longest_digit(map), targets, groups);
+  const dim3 grid(M, (targets + v.targets - 1) / v.targets, groups);
+  if (v.targets == 3)
     k_bconv_outer<LOGM, 3, false, Map><<<grid, kThreads, 0, s>>>(map, c->log_n, c->d_pk, tw, ti);
-  } else {
-    const dim3 grid(M, targets, groups);
+  else if (fuse)
     k_bconv_outer<LOGM, 1, CAN, Map><<<grid, kThreads, 0, s>>>(map, c->log_n, c->d_pk, tw, ti);
-  }
+  else
+    k_bconv_outer<LOGM, 1, false, Map><<<grid, kThreads, 0, s>>>(map, c->log_n, c->d_pk, tw, ti);
   return hipGetLastError();
 }
 
