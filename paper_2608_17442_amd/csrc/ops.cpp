@@ -323,7 +323,7 @@ int key_switch_batch(Context* c, uint32_t level, const std::vector<KsSource>& sr
       continue;
     }
     HIPCK(k_ip_launch(c, t, nkeys, S.ext, S.acc, level, T->md_pinv, s));
-    if (small_moddown_fits(c, t, nj, rescale_rows ? rescale_rows : level)) {
+    if (small_moddown_fits(c, t, nj, level, rescale_rows)) {
       HIPCK(launch_small_moddown(c, *T, t, nj, S.acc, level, rescale_rows, s));
       continue;
     }

@@ -136,7 +136,8 @@ hipError_t k_ip_launch(const Context* c, const KsTable& tab, uint32_t nkeys, con
 bool small_modup_fits(const Context* c, uint32_t nsrc, uint32_t level);
 hipError_t launch_small_modup(const Context* c, const LevelTables& T, const KsTable& tab,
                               uint32_t nsrc, uint64_t* ext, uint32_t level, hipStream_t s);
-bool small_moddown_fits(const Context* c, const KsTable& t, uint32_t njobs, uint32_t rows);
+bool small_moddown_fits(const Context* c, const KsTable& t, uint32_t njobs, uint32_t level,
+                        uint32_t rescale_rows);
 hipError_t launch_small_moddown(const Context* c, const LevelTables& T, const KsTable& tab,
                                 uint32_t njobs, const uint64_t* acc, uint32_t level,
                                 uint32_t rescale_rows, hipStream_t s);

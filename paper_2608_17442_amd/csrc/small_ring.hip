@@ -13,11 +13,12 @@
 // the threads that way, and held by the workgroups of a transform (which saves a
 // launch more) its loads took longer than the launch, 45 us for that rotation.
 // The same residues: every step is exact modulo its prime.  The repeated
-// transforms pay while the launches are small (kSmallFill) and a digit has at most
-// three primes; larger batches take the general pipeline.
+// transforms pay while the launches are small (kSmallFill) and at most three primes
+// are converted; larger batches take the general pipeline.
 #include "block4096.hpp"
 #include "fesc_internal.hpp"
 #include "ops.hpp"
+#include "small_ring_rule.hpp"
 
 namespace fesc {
 
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(kThreads) void k_small_moddown(
   double y[16];
 #pragma unroll
   for (int r = 0; r < 16; ++r) y[r] = 0.0;
-  for (uint32_t a = 0; a < nd; ++a) {  // at most four digits: below 3 q
+  for (uint32_t a = 0; a < nd; ++a) {  // at most three digits: below 2 q
     const uint32_t row = first + a, prime = row < level ? row : L + (row - level);
     const PrimeK P = pk[prime];
     const double2 c = f[a], h = hat[(size_t)i * nd + a];
@@ -215,28 +216,10 @@ __global__ __launch_bounds__(kThreads) void k_small_rescale(RsTable tab, uint32_
   }
 }
 
-
-// Workgroups times digit primes up to which the repeated transforms cost less than
-// the launches that they save (four workgroups of one prime's work on each CU).
-// Rotations with either fusion alone, us, general -> fused, 50-bit primes:
-//   ModUp   alpha 1, 8 rows: 45 -> 38 (72 workgroups), 69 -> 61 (576);
-//           alpha 3, 15 rows: 46.7 -> 45.6 (90), 57 -> 63 (360), 78 -> 82 (720)
-//   ModDown alpha 1, 15 rows: 52 -> 45 (30), 315 -> 300 (960);
-//           alpha 3, 24 rows: 78 -> 73 (192), 110 -> 112 (384), 182 -> 185 (768)
-// and one rotation with both 41 -> 27 (3 rows, alpha 1), 46 -> 42 (9 rows, alpha 3),
-// 48 -> 37 (15 rows, alpha 2).
-constexpr uint32_t kSmallFill = 1024;
-
-bool overlap(const uint64_t* a, size_t na, const uint64_t* b, size_t nb) {
-  return a < b + nb && b < a + na;
-}
-
 }  // namespace
 
 bool small_modup_fits(const Context* c, uint32_t nsrc, uint32_t level) {
-  const uint32_t dnum = (level + c->alpha - 1) / c->alpha;
-  return c->log_n == 12 && c->alpha <= 3 &&
-         c->alpha * nsrc * dnum * (level + c->alpha) <= kSmallFill;
+  return small_modup_pays(c->log_n, c->alpha, nsrc, level);
 }
 
 hipError_t launch_small_modup(const Context* c, const LevelTables& T, const KsTable& tab,
@@ -248,9 +231,10 @@ hipError_t launch_small_modup(const Context* c, const LevelTables& T, const KsTa
   return hipGetLastError();
 }
 
-bool small_moddown_fits(const Context* c, const KsTable& t, uint32_t njobs, uint32_t rows) {
-  return c->log_n == 12 && c->alpha <= 3 && t.fold == 1 &&
-         c->alpha * 2 * njobs * rows <= kSmallFill;
+bool small_moddown_fits(const Context* c, const KsTable& t, uint32_t njobs, uint32_t level,
+                        uint32_t rescale_rows) {
+  return t.fold == 1 && small_moddown_pays(c->log_n, c->alpha, rescale_rows != 0, njobs,
+                                           rescale_rows ? rescale_rows : level);
 }
 
 hipError_t launch_small_moddown(const Context* c, const LevelTables& T, const KsTable& tab,
@@ -266,7 +250,7 @@ hipError_t launch_small_moddown(const Context* c, const LevelTables& T, const Ks
 
 bool small_rescale_fits(const Context* c, const RsTable& t, uint32_t count, uint32_t last,
                         uint32_t rows) {
-  if (c->log_n != 12 || 2 * count * rows > kSmallFill) return false;
+  if (!small_rescale_pays(c->log_n, count, rows)) return false;
   for (uint32_t i = 0; i < count; ++i)  // every row's workgroup reads the last limbs
     for (uint32_t j = 0; j < count; ++j)
       if (overlap(t.out[i], (size_t)2 * rows * kN, t.in[j] + (size_t)2 * last * kN, 2 * kN))
