@@ -10,7 +10,8 @@
 // an inverse DFT of half the length.  Per plaintext:
 //   1. inverse NTT of the limbs into scratch (canonical residues, coefficient
 //      form);
-//   2. k_dec_outer: the centred integers m_k from their residues by a
+//   2. k_dec_outer (past 32 limbs, or with primes more than a factor of two apart,
+//      k_dec_crt before it, N > 4096): the centred integers m_k from their residues by a
 //      mixed-radix CRT with balanced digits (Garner's method: v_0 = [y_0], v_i =
 //      [(...((y_i - v_0) q_0^-1 - v_1) q_1^-1 ...) q_(i-1)^-1]_(q_i), each in
 //      (-q_i/2, q_i/2]), so m_k = v_0 + q_0 (v_1 + q_1 (v_2 + ...)) exactly; the
@@ -66,67 +67,83 @@ __device__ __forceinline__ double2 mul_root(double2 a, const double2* __restrict
 }
 
 // Centred integers of NC coefficients, r[c * off + i * n] their residues at limb
-// i.  LMAX > 0: all digits in registers, limbs past `level` carried along as
-// zeros (LMAX the next multiple of 4), every prime within a factor of two of
-// the others: |t - v_j| < 2 q_i then, the product stays within 0.9 q_i and
-// red_bal's quotient is exact.  LMAX == 0: any level and primes.
+// i, all digits in registers.  Limbs from `level` on (LMAX is the next multiple of
+// 4) repeat the last limb; the Horner sum leaves them out.  Every prime is within a
+// factor of two of the others: |t - v_j| < 2 q_i then, the product stays within
+// 0.9 q_i and red_bal's quotient is exact.
 template <int LMAX, int NC>
 __device__ __forceinline__ void crt(const uint64_t* __restrict__ r, size_t off, uint32_t level,
                                     uint32_t L, uint32_t n, const PrimeK* __restrict__ pk,
                                     const double2* __restrict__ garner, double (&m)[NC]) {
-  if constexpr (LMAX > 0) {
-    double t[NC][LMAX];
+  double t[NC][LMAX];
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int i = 0; i < LMAX; ++i)
-        t[c][i] = u2d(r[c * off + (size_t)min((uint32_t)i, level - 1) * n]);
+    for (int i = 0; i < LMAX; ++i)
+      t[c][i] = u2d(r[c * off + (size_t)min((uint32_t)i, level - 1) * n]);
 #pragma unroll
-    for (int j = 0; j < LMAX; ++j) {
-      const uint32_t ju = min((uint32_t)j, level - 1);
-      const double qj = pk[ju].q, qinvj = pk[ju].qinv;
+  for (int j = 0; j < LMAX; ++j) {
+    const uint32_t ju = min((uint32_t)j, level - 1);
+    const double qj = pk[ju].q, qinvj = pk[ju].qinv;
 #pragma unroll
-      for (int c = 0; c < NC; ++c) t[c][j] = red_bal(t[c][j], qj, qinvj);
+    for (int c = 0; c < NC; ++c) t[c][j] = red_bal(t[c][j], qj, qinvj);
 #pragma unroll
-      for (int i = j + 1; i < LMAX; ++i) {
-        const uint32_t iu = min((uint32_t)i, level - 1);
-        const double w = garner[(size_t)iu * L + min((uint32_t)j, iu)].x;
-        const double q = pk[iu].q, qinv = pk[iu].qinv;
+    for (int i = j + 1; i < LMAX; ++i) {
+      const uint32_t iu = min((uint32_t)i, level - 1);
+      const double w = garner[(size_t)iu * L + min((uint32_t)j, iu)].x;
+      const double q = pk[iu].q, qinv = pk[iu].qinv;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) t[c][i] = mm_var(t[c][i] - t[c][j], w, q, qinv);
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < NC; ++c) m[c] = 0.0;
-#pragma unroll
-    for (int i = LMAX - 1; i >= 0; --i) {
-      const double q = pk[min((uint32_t)i, level - 1)].q;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) m[c] = (uint32_t)i < level ? t[c][i] + q * m[c] : 0.0;
-    }
-  } else {
-    for (int c = 0; c < NC; ++c) {
-      double v[FESC_MAX_PRIMES];
-      for (uint32_t i = 0; i < level; ++i) {
-        const PrimeK P = pk[i];
-        double t = u2d(r[c * off + (size_t)i * n]);
-        const double2* gi = garner + (size_t)i * L;
-        for (uint32_t j = 0; j < i; ++j) {  // t = (t - v_j) q_j^-1 mod q_i
-          const double2 w = gi[j];
-          t = red_bal(mm_shoup(red_bal(t - v[j], P.q, P.qinv), w.x, w.y, P.q), P.q, P.qinv);
-        }
-        v[i] = center(red_full(t, P.q, P.qinv), P.q);
-      }
-      double s = v[level - 1];
-      for (uint32_t i = level - 1; i-- > 0;) s = v[i] + pk[i].q * s;
-      m[c] = s;
+      for (int c = 0; c < NC; ++c) t[c][i] = mm_var(t[c][i] - t[c][j], w, q, qinv);
     }
   }
+#pragma unroll
+  for (int c = 0; c < NC; ++c) m[c] = 0.0;
+#pragma unroll
+  for (int i = LMAX - 1; i >= 0; --i) {
+    const double q = pk[min((uint32_t)i, level - 1)].q;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) m[c] = (uint32_t)i < level ? t[c][i] + q * m[c] : 0.0;
+  }
+}
+
+// The same for any level and primes, one coefficient; its digits do not fit in
+// registers.
+__device__ __forceinline__ double crt_any(const uint64_t* r, uint32_t level, uint32_t L,
+                                          uint32_t n, const PrimeK* __restrict__ pk,
+                                          const double2* __restrict__ garner) {
+  double v[FESC_MAX_PRIMES];
+  for (uint32_t i = 0; i < level; ++i) {
+    const PrimeK P = pk[i];
+    double t = u2d(r[(size_t)i * n]);
+    const double2* gi = garner + (size_t)i * L;
+    for (uint32_t j = 0; j < i; ++j) {  // t = (t - v_j) q_j^-1 mod q_i
+      const double2 w = gi[j];
+      t = red_bal(mm_shoup(red_bal(t - v[j], P.q, P.qinv), w.x, w.y, P.q), P.q, P.qinv);
+    }
+    v[i] = center(red_full(t, P.q, P.qinv), P.q);
+  }
+  double m = v[level - 1];
+  for (uint32_t i = level - 1; i-- > 0;) m = v[i] + pk[i].q * m;
+  return m;
+}
+
+// crt_any of coefficient k of plaintext blockIdx.y, stored as fp64 over its residue
+// at limb 0.  Bound by the chain through the digits, so every coefficient has a
+// thread of its own: with both coefficients of an output in one thread of
+// k_dec_outer a call of 36 limbs took, us, N = 2^13 210 (now 119; four plaintexts 228,
+// now 140), N = 2^16 254 (154; four 434, 322; sixteen, where the chip is full, 1020, 1024).
+__global__ __launch_bounds__(kThreads) void k_dec_crt(uint64_t* __restrict__ res, uint32_t level,
+                                                      uint32_t L, uint32_t n,
+                                                      const PrimeK* __restrict__ pk,
+                                                      const double2* __restrict__ garner) {
+  uint64_t* r = res + (size_t)blockIdx.y * level * n + blockIdx.x * kThreads + threadIdx.x;
+  *reinterpret_cast<double*>(r) = crt_any(r, level, L, n, pk, garner);
 }
 
 // CRT, twist and R-point columns.  A workgroup takes 256 / R columns of
 // plaintext blockIdx.y: thread (n1, column) forms the twisted input of index
-// k = 4096 n1 + n2, thread (k1, column) the output X[k1][n2].
+// k = 4096 n1 + n2, thread (k1, column) the output X[k1][n2].  LMAX == 0, of
+// the folded form: k_dec_crt has run, the coefficients stand at limb 0.
 template <int LMAX, bool FOLD>
 __global__ __launch_bounds__(kThreads) void k_dec_outer(const uint64_t* __restrict__ res,
                                                         uint32_t level, uint32_t L, uint32_t n,
@@ -139,7 +156,16 @@ __global__ __launch_bounds__(kThreads) void k_dec_outer(const uint64_t* __restri
   const uint32_t i1 = t / cols, col = t % cols;
   const uint32_t n2 = blockIdx.x * cols + col, k = kRow * i1 + n2;
   double m[FOLD ? 2 : 1];
-  crt<LMAX, FOLD ? 2 : 1>(res + (size_t)b * level * n + k, n / 2, level, L, n, pk, garner, m);
+  const uint64_t* r = res + (size_t)b * level * n + k;
+  if constexpr (LMAX > 0) {
+    crt<LMAX, FOLD ? 2 : 1>(r, n / 2, level, L, n, pk, garner, m);
+  } else if constexpr (FOLD) {
+    const double* rd = reinterpret_cast<const double*>(r);
+    m[0] = rd[0];
+    m[1] = rd[n / 2];
+  } else {
+    m[0] = crt_any(r, level, L, n, pk, garner);
+  }
   const double2 w0 = T[k];
   double2 x{m[0] * w0.x, -m[0] * w0.y};
   if constexpr (FOLD) {  // zeta^(k + N/2) from the table as well, not as i zeta^k
@@ -306,7 +332,14 @@ int op_decode_plain(Context* c, const uint64_t* pt, uint32_t count, uint32_t lev
       case 6: launch_outer<24>(c, limbs, level, R, fold, m, X, s); break;
       case 7: launch_outer<28>(c, limbs, level, R, fold, m, X, s); break;
       case 8: launch_outer<32>(c, limbs, level, R, fold, m, X, s); break;
-      default: launch_outer<0>(c, limbs, level, R, fold, m, X, s); break;
+      default:
+        if (fold) {
+          k_dec_crt<<<dim3(n / kThreads, m), kThreads, 0, s>>>(limbs, level, c->L, n, c->d_pk,
+                                                               c->d_garner);
+          if (int rc = hip_check(hipGetLastError(), "k_dec_crt")) return rc;
+        }
+        launch_outer<0>(c, limbs, level, R, fold, m, X, s);
+        break;
     }
     if (int rc = hip_check(hipGetLastError(), "k_dec_outer")) return rc;
     double2* zb = z + (size_t)b0 * (n / 2);

@@ -165,12 +165,14 @@ def test_decode_plain_errors():
     assert torch.count_nonzero(out).item() == 0    # the zero plaintext decodes to zeros
 
 
-# Every register bucket of the CRT (levels 1..32 in steps of 4), past it (33
-# limbs), primes too far apart for it, one row (N = 4096) and 1, 2, 4, 8 of them
+# Every register bucket of the CRT (levels 1..32 in steps of 4, full and with a
+# repeated limb), past it (33 limbs and more), primes too far apart for it, one row
+# (N = 4096) and 1, 2, 4, 8 of them
 @pytest.mark.parametrize("log_n,bits,level,count", [
     (12, (50,), 3, 2), (12, (30,), 33, 1), (12, (30,), 32, 1), (12, (36, 30, 50), 6, 1),
     (13, (30,), 5, 3), (13, (50, 30), 7, 2), (13, (36,), 12, 1), (14, (45,), 10, 2),
     (14, (36,), 21, 1), (15, (50,), 20, 2), (15, (36,), 27, 1), (16, (36,), 2, 2),
+    (13, (30,), 33, 3), (14, (27,), 37, 1), (16, (27,), 34, 1), (15, (50, 36), 3, 2),
 ])
 def test_decode_plain_full_range(log_n, bits, level, count):
     """Uniform residues: coefficients over the whole of (-Q/2, Q/2], decoded at
