@@ -170,12 +170,14 @@ __device__ __forceinline__ void inv_transform(const UniTw& u, const double* lt, 
   gs_st<8, kGs2.m[3]>(x, TwU{u.top}, q, qinv);
 }
 
-// 16 consecutive residues at p (two 16-byte loads per pair).
+// 16 consecutive residues at p, in 16-byte loads.  Callers' buffers are as aligned as
+// their 64-bit words, which is all that the loads ask for.
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2), aligned(8)));
 __device__ __forceinline__ void load16(const uint64_t* p, double (&x)[16]) {
-  const ulonglong2* v = reinterpret_cast<const ulonglong2*>(p);
+  const u64x2* v = reinterpret_cast<const u64x2*>(p);
 #pragma unroll
   for (int r = 0; r < 16; r += 2) {
-    const ulonglong2 w = v[r / 2];
+    const u64x2 w = v[r / 2];
     x[r] = u2d(w.x);
     x[r + 1] = u2d(w.y);
   }

@@ -198,6 +198,23 @@ def test_decode_plain_full_range(log_n, bits, level, count):
         assert np.linalg.norm(got[b] - want) <= 1e-14 * np.linalg.norm(want)
 
 
+@pytest.mark.parametrize("log_n", [12, 13])
+def test_decode_plain_at_odd_words(log_n):
+    """A plaintext that starts at an odd 64-bit word of its buffer decodes to the
+    same bits as one at a 16-byte boundary."""
+    P = C.params_small(log_n, 50, 3, 1)
+    ctx = F.Context(log_n, P.q, P.p)
+    pth = to_dev(synth.uniform_residues(53, "odd", P.qs(3), P.n, 0)).reshape(-1)
+    odd = torch.zeros(pth.numel() + 1, dtype=torch.int64, device="cuda")[1:]
+    odd.copy_(pth)
+    assert pth.data_ptr() % 16 == 0 and odd.data_ptr() % 16 == 8
+    outs = [torch.zeros(1, P.n // 2, dtype=torch.complex128, device="cuda") for _ in range(2)]
+    step(f"decode_plain N=2^{log_n} at an odd word")
+    for pt, out in zip((pth, odd), outs):
+        ctx.decode_plain(pt, 1, 3, 2.0 ** 40, out)
+    assert torch.equal(outs[0], outs[1])
+
+
 # Every split of the fused lift (one row at N = 4096, 1 .. 4 stages in its pass),
 # coefficients below and past 2^51, which are lifted by different code, and both
 # in one plaintext; counts that take one or several rows of limbs per workgroup
