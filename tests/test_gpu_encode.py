@@ -167,12 +167,14 @@ def test_decode_plain_errors():
 
 # Every register bucket of the CRT (levels 1..32 in steps of 4, full and with a
 # repeated limb), past it (33 limbs and more), primes too far apart for it, one row
-# (N = 4096) and 1, 2, 4, 8 of them
+# (N = 4096) and 1, 2, 4, 8 of them, more plaintexts than one round's scratch takes
 @pytest.mark.parametrize("log_n,bits,level,count", [
     (12, (50,), 3, 2), (12, (30,), 33, 1), (12, (30,), 32, 1), (12, (36, 30, 50), 6, 1),
     (13, (30,), 5, 3), (13, (50, 30), 7, 2), (13, (36,), 12, 1), (14, (45,), 10, 2),
     (14, (36,), 21, 1), (15, (50,), 20, 2), (15, (36,), 27, 1), (16, (36,), 2, 2),
-    (13, (30,), 33, 3), (14, (27,), 37, 1), (16, (27,), 34, 1), (15, (50, 36), 3, 2),
+    (12, (50,), 4, 1), (14, (50,), 8, 1), (16, (50,), 15, 1), (13, (36,), 16, 1),
+    (14, (50,), 18, 1), (13, (36,), 24, 1), (12, (36,), 28, 1), (15, (30,), 31, 1),
+    (12, (36,), 2, 40), (13, (36,), 2, 50), (13, (30,), 33, 3), (14, (27,), 37, 1), (16, (27,), 34, 1), (15, (50, 36), 3, 2),
 ])
 def test_decode_plain_full_range(log_n, bits, level, count):
     """Uniform residues: coefficients over the whole of (-Q/2, Q/2], decoded at
@@ -217,10 +219,12 @@ def test_decode_plain_at_odd_words(log_n):
 
 # Every split of the fused lift (one row at N = 4096, 1 .. 4 stages in its pass),
 # coefficients below and past 2^51, which are lifted by different code, and both
-# in one plaintext; counts that take one or several rows of limbs per workgroup
+# in one plaintext; counts that take one or several rows of limbs per workgroup,
+# and several rounds (by the scratch, by the plaintexts' bytes)
 @pytest.mark.parametrize("log_n,bits,level,count,log_scale", [
     (12, 50, 3, 2, 58), (13, 36, 5, 3, 40), (13, 50, 3, 1, 60), (14, 45, 4, 70, 44),
     (14, 50, 7, 1, 59), (15, 50, 5, 40, 40), (15, 36, 6, 2, 61), (16, 50, 3, 2, 61),
+    (12, 36, 2, 45, 30), (15, 50, 24, 50, 40),
 ])
 def test_encode_plain_lift(log_n, bits, level, count, log_scale):
     """Every limb is the exact transform of one integer vector (its centred CRT),
