@@ -1,8 +1,8 @@
 """GPU parity of the fused key switch and rescale at N = 4096: digits of one to
 three primes, a last digit of one prime, seed-expanded and stored keys in one
 batch, product sources, batches on both sides of the sizes at which the general
-pipeline takes over, and outputs that overlap what the batch reads.  Bit-exact
-against the oracle on uniform residues."""
+pipeline takes over, rescales of several ciphertexts, in place and over the last
+limb that they read.  Bit-exact against the oracle on uniform residues."""
 import numpy as np
 import pytest
 import torch
@@ -95,3 +95,42 @@ def test_small_ring(bits, L, alpha, level, count):
     ctx.rescale(dev[0], dev[0], level)
     want = C.rescale(P, C.rotate(P, host[0], r[0], keys))
     _eq(dev[0][:want.size], want, "rescale in place")
+
+
+# 16 ciphertexts per launch: 16 x 32 rows are the limit of the fused rescale, a
+# rest of one takes it on either side
+@pytest.mark.parametrize("level,n_out", [(2, 3), (33, 17), (34, 16), (34, 17)])
+def test_rescale_of_several(level, n_out):
+    """The rescale of a matrix-vector product's outputs (one term each)."""
+    from paper_2608_17442_amd import fesc as F
+    P = C.params_small(12, 36, level, 3)
+    ctx = F.Context(P.log_n, P.q, P.p)
+    x = _residues(P, level, 0)
+    pool = [synth.uniform_residues(SEED, "d", P.qs(level), P.n, i) for i in range(3)]
+    dev = [to_dev(p).reshape(-1) for p in pool]
+    plan = F.MatvecPlan(ctx, level, 1, n_out, 1, 1, 1, False, True,
+                        diags=[dev[b % 3] for b in range(n_out)])
+    outs = [torch.zeros((level - 1) * 2 * P.n, dtype=torch.int64, device="cuda")
+            for _ in range(n_out)]
+    step(f"rescale of {n_out} outputs, level {level}")
+    plan([to_dev(x).reshape(-1)], outs)
+    want = [C.rescale(P, C.mul_plain(P, x, p)) for p in pool]
+    for b, o in enumerate(outs):
+        _eq(o, want[b % 3], f"output {b}")
+
+
+@pytest.mark.parametrize("log_n", [12, 13])
+def test_rescale_over_its_last_limb(log_n):
+    """An output that starts at the last limb of the input: every row reads that
+    limb, so the rows cannot be one launch."""
+    from paper_2608_17442_amd import fesc as F
+    level = 5
+    P = C.params_small(log_n, 50, level, 1)
+    ctx = F.Context(P.log_n, P.q, P.p)
+    x, limb = _residues(P, level, 0), 2 * P.n
+    buf = torch.zeros((2 * level - 2) * limb, dtype=torch.int64, device="cuda")
+    buf[:level * limb] = to_dev(x).reshape(-1)
+    step(f"rescale over the last limb, N=2^{log_n}")
+    ctx.rescale(buf[:level * limb], buf[(level - 1) * limb:], level)
+    _eq(buf[(level - 1) * limb:], C.rescale(P, x), "over the last limb")
+    _eq(buf[:(level - 1) * limb], x[:-1], "the other limbs")
