@@ -21,7 +21,7 @@ def _gpu():
 
 
 SPLIT = [(12, 2, n_out, terms)
-         for n_out, terms in [(1, 1), (1, 7), (1, 8), (1, 33), (2, 9), (2, 32), (3, 8), (4, 35),
+         for n_out, terms in [(1, 1), (1, 7), (1, 8), (1, 33), (2, 7), (2, 9), (2, 32), (3, 8), (4, 35),
                               (5, 8), (7, 3), (8, 17), (9, 6), (12, 9), (13, 5), (16, 8), (17, 9),
                               (22, 4), (24, 9), (25, 3), (33, 2), (36, 5)]]
 WHOLE = [(16, 2, 1, 9), (16, 2, 3, 8), (16, 2, 6, 9), (16, 2, 24, 3), (16, 2, 17, 2)]
