@@ -109,4 +109,50 @@ __device__ __forceinline__ void gs_st(double (&x)[16], TW tw, double q, double q
   }
 }
 
+// The outer pass's stages on M-point columns, M = 2^LOGM: value m of column j in
+// x[j M + m], tw the prime's power table; stage s uses psi_rev[2^s + m / 2^(LOGM - s)].
+// Forward, from canonical residues or balanced values (below kCtOuter q).
+template <int LOGM>
+__device__ __forceinline__ void fwd_columns(double (&x)[16], const double* __restrict__ tw,
+                                            double q, double qinv) {
+  constexpr int M = 1 << LOGM, C = 16 / M;
+#pragma unroll
+  for (int s = 0; s < LOGM; ++s) {
+    const int H = M >> (s + 1);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      if (m & H) continue;
+      const double w = tw[(1 << s) + (m >> (LOGM - s))];
+#pragma unroll
+      for (int j = 0; j < C; ++j) {
+        const double u = x[j * M + m], v = mm_var(x[j * M + m + H], w, q, qinv);
+        x[j * M + m] = u + v;
+        x[j * M + m + H] = u - v;
+      }
+    }
+  }
+}
+
+// Inverse: the same stages in reverse order (sums reduced as kGsOut says).
+template <int LOGM>
+__device__ __forceinline__ void inv_columns(double (&x)[16], const double* __restrict__ tw,
+                                            double q, double qinv) {
+  constexpr int M = 1 << LOGM, C = 16 / M;
+#pragma unroll
+  for (int s = LOGM - 1; s >= 0; --s) {
+    const int H = M >> (s + 1);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      if (m & H) continue;
+      const double w = tw[(1 << s) + (m >> (LOGM - s))];
+#pragma unroll
+      for (int j = 0; j < C; ++j) {
+        const double u = x[j * M + m], v = x[j * M + m + H];
+        x[j * M + m] = (kGsOut.m[LOGM - 1 - s] >> m) & 1u ? red_bal(u + v, q, qinv) : u + v;
+        x[j * M + m + H] = mm_var(u - v, w, q, qinv);
+      }
+    }
+  }
+}
+
 }  // namespace fesc

@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "butterfly.hpp"
 #include "fesc_internal.hpp"
 #include "ops.hpp"
 
@@ -260,21 +261,7 @@ __global__ __launch_bounds__(kThreads) void k_enc_lift_outer(const int64_t* __re
 #pragma unroll
       for (int r = 0; r < 16; ++r) x[r] = lift_any(v[r], two32, q, qinv);
     }
-#pragma unroll
-    for (int s = 0; s < LOGM; ++s) {
-      const int H = M >> (s + 1);
-#pragma unroll
-      for (int m = 0; m < M; ++m) {
-        if (m & H) continue;
-        const double w = tw[(1 << s) + (m >> (LOGM - s))];
-#pragma unroll
-        for (int j = 0; j < C; ++j) {
-          const double u = x[j * M + m], z = mm_var(x[j * M + m + H], w, q, qinv);
-          x[j * M + m] = u + z;
-          x[j * M + m + H] = u - z;
-        }
-      }
-    }
+    fwd_columns<LOGM>(x, tw, q, qinv);
     double* out = reinterpret_cast<double*>(pt) + ((size_t)b * rows + i) * n + c0;
 #pragma unroll
     for (int j = 0; j < C; ++j)

@@ -68,8 +68,7 @@ namespace {
 
 // M = 2^LOGM point columns at stride 4096; a thread holds C = 16/M columns,
 // c0 + 256 j (j < C), value m of column j in x[j*M + m].  Grid x = M.
-// Stage s (distance 4096 * M/2^(s+1)) uses psi_rev[2^s + m / 2^(LOGM-s)].
-// Forward stages from canonical residues reduce nothing (below kCtOuter q).
+// Stage s has distance 4096 * M/2^(s+1).
 template <int LOGM>
 __global__ __launch_bounds__(kThreads) void k_fwd_outer(RowSel rs, uint32_t log_n,
                                                         const PrimeK* __restrict__ pk,
@@ -87,21 +86,7 @@ __global__ __launch_bounds__(kThreads) void k_fwd_outer(RowSel rs, uint32_t log_
   for (int j = 0; j < C; ++j)
 #pragma unroll
     for (int m = 0; m < M; ++m) x[j * M + m] = u2d(row[c0 + kThreads * j + kBlock * m]);
-#pragma unroll
-  for (int s = 0; s < LOGM; ++s) {
-    const int H = M >> (s + 1);
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      if (m & H) continue;
-      const double w = tw[(1 << s) + (m >> (LOGM - s))];
-#pragma unroll
-      for (int j = 0; j < C; ++j) {
-        const double u = x[j * M + m], v = mm_var(x[j * M + m + H], w, q, qinv);
-        x[j * M + m] = u + v;
-        x[j * M + m + H] = u - v;
-      }
-    }
-  }
+  fwd_columns<LOGM>(x, tw, q, qinv);
   double* rowd = reinterpret_cast<double*>(row);
 #pragma unroll
   for (int j = 0; j < C; ++j)
@@ -131,29 +116,6 @@ struct InvDigit {
     reinterpret_cast<double*>(row)[k] = red_bal(mm_shoup(x, c.x, c.y, P.q), P.q, P.qinv);
   }
 };
-
-// The inverse stages of the outer pass on the columns x[j M + m], in reverse
-// order (sums reduced as kGsOut says).
-template <int LOGM>
-__device__ __forceinline__ void inv_columns(double (&x)[16], const double* __restrict__ tw,
-                                            double q, double qinv) {
-  constexpr int M = 1 << LOGM, C = 16 / M;
-#pragma unroll
-  for (int s = LOGM - 1; s >= 0; --s) {
-    const int H = M >> (s + 1);
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      if (m & H) continue;
-      const double w = tw[(1 << s) + (m >> (LOGM - s))];
-#pragma unroll
-      for (int j = 0; j < C; ++j) {
-        const double u = x[j * M + m], v = x[j * M + m + H];
-        x[j * M + m] = (kGsOut.m[LOGM - 1 - s] >> m) & 1u ? red_bal(u + v, q, qinv) : u + v;
-        x[j * M + m + H] = mm_var(u - v, w, q, qinv);
-      }
-    }
-  }
-}
 
 // Inverse: the columns, then the final store (N^-1 scaling included).
 template <int LOGM, class St>
@@ -272,21 +234,7 @@ __global__ __launch_bounds__(kThreads) void k_bconv_outer(Map map, uint32_t log_
       const double* tw = twf + (size_t)prime[i] * n;
 #pragma unroll
       for (int v = 0; v < 16; ++v) x[v] = red_bal(x[v], q, qinv);
-#pragma unroll
-      for (int s = 0; s < LOGM; ++s) {
-        const int H = M >> (s + 1);
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-          if (m & H) continue;
-          const double w = tw[(1 << s) + (m >> (LOGM - s))];
-#pragma unroll
-          for (int j = 0; j < C; ++j) {
-            const double u = x[j * M + m], v = mm_var(x[j * M + m + H], w, q, qinv);
-            x[j * M + m] = u + v;
-            x[j * M + m + H] = u - v;
-          }
-        }
-      }
+      fwd_columns<LOGM>(x, tw, q, qinv);
       double* outd = reinterpret_cast<double*>(out);
 #pragma unroll
       for (int j = 0; j < C; ++j)
@@ -538,21 +486,7 @@ __device__ __forceinline__ void bconv_mfma(const Map& map, const PrimeK* __restr
       for (int v = 0; v < 16; ++v) out[c + at(v)] = to_res_2q(x[v], q, qinv);
     } else {
       const double* tw = twf + (size_t)prime * n;
-#pragma unroll
-      for (int s = 0; s < LOGM; ++s) {
-        const int H = M >> (s + 1);
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-          if (m & H) continue;
-          const double w = tw[(1 << s) + (m >> (LOGM - s))];
-#pragma unroll
-          for (int j = 0; j < C; ++j) {
-            const double u = x[j * M + m], z = mm_var(x[j * M + m + H], w, q, qinv);
-            x[j * M + m] = u + z;
-            x[j * M + m + H] = u - z;
-          }
-        }
-      }
+      fwd_columns<LOGM>(x, tw, q, qinv);
       double* outd = reinterpret_cast<double*>(map.out(g, trow));
 #pragma unroll
       for (int v = 0; v < 16; ++v) outd[c + at(v)] = x[v];
