@@ -100,9 +100,11 @@ struct TwGen {
   }
 };
 
-// The 12 stages on values already loaded by fwd_load; u: the uniform twiddles,
-// lt: the staged ones (written before the first barrier), b:
-// psi_rev[(N + B) / 2 + 8 t].
+// The 12 forward stages: thread t comes with the values t + 256 r of the block in
+// x[r] and ends with those at 16 t + r.  u: the uniform twiddles, lt: the staged ones
+// (written before the first barrier), b: psi_rev[(N + B) / 2 + 8 t].  Uses all of
+// `lds`; the caller needs a barrier before touching it again unless it only
+// writes the words it is handed (positions 16 t + r).
 __device__ __forceinline__ void fwd_transform(const UniTw& u, const double* lt, double b,
                                               double q, double qinv, double* lds,
                                               double (&x)[16]) {

@@ -22,10 +22,10 @@
 //      radix-16 register steps with LDS transposes, and the store of z_j =
 //      v[p_j] / Delta through the encoder's inverse slot table.
 // For N = 4096 (N/2 = 2048) the full-length DFT is one row and half its outputs
-// are dropped.  24 plaintexts at N = 2^16, 15 limbs: 217 us, 77 of them the CRT
-// (VALU: 120 products per coefficient), 124 the inverse NTT, 23 the rows; with a
-// spilling CRT, sixteen radix-2 passes of full length and a copy before the
-// inverse NTT it was 589 us.  The error against long doubles fell with it (2-norm
+// are dropped.  24 plaintexts at N = 2^16, 15 limbs: 220 us, of which, traced, 69 +
+// 56 the inverse NTT, 74 k_dec_outer (VALU: 120 products per coefficient), 23 the rows;
+// with a spilling CRT, sixteen radix-2 passes of full length and a copy before the
+// inverse NTT it was 588 us.  The error against long doubles fell with it (2-norm
 // 4.6e-16 from 6.3e-16: fewer roundings, smaller angles).
 // Every twiddle is an entry of the encoder's table T[k] = exp(-i pi k / N), here
 // conjugated.

@@ -14,8 +14,8 @@
 //     the twist zeta^-k, scales and rounds, storing m in the transform's
 //     digit-reversed order;
 // then the lift to the RNS limbs inside the first forward NTT pass and the second
-// pass of every limb (64 plaintexts at N = 2^16, 16 limbs: 423 us; with a lift of
-// its own, gathering m once per limb, 801 us).  Every twiddle is an entry of one table
+// pass of every limb (64 plaintexts at N = 2^16, 16 limbs: 432 us; with a lift of
+// its own, gathering m once per limb, 815 us).  Every twiddle is an entry of one table
 // T[k] = exp(-i pi k / N), k < 2N.
 #include <algorithm>
 #include <cmath>

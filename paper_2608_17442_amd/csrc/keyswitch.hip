@@ -3,7 +3,8 @@
 // (ntt.hip; for small batches at N = 4096 steps 1 and 2, and step 4, are one
 // launch each, small_ring.hip), fused into their passes:
 //   1. inverse NTT of each source polynomial, reading the caller's rows
-//      directly; its last pass stores the centred ModUp digits
+//      directly; its last pass (the conversion itself in small batches) forms
+//      the centred ModUp digits
 //          x_a = [c_a * (Q_D/q_a)^-1]_{q_a} in (-q_a/2, q_a/2)  (fp64);
 //   2. ModUp: y mod m = sum_a x_a * ((Q_D/q_a) mod m) for every extended row
 //      m outside digit D, fused with the first forward pass; second pass;

@@ -154,7 +154,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) v
 // pass) the canonical residue is stored instead.  FUSE: the digit rows still
 // hold the inverse transform's intermediate; its columns are finished here
 // (inv_columns and InvDigit's factor), which saves a launch and is done again by
-// every workgroup of a column, so only in small launches.  Targets vary fastest after
+// every workgroup of a column, so only where that costs less (valu_conversion).
+// Targets vary fastest after
 // the column block, so all targets of a column block run together and read
 // its digit rows from L2; with M a multiple of 8 a column block also stays on
 // one XCD (workgroups are dealt to the 8 XCDs round-robin).
@@ -512,10 +513,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 
 // ------------------------------------------------------------- inner pass
 
-// The last 12 forward stages on block B (offset of its first value) of
-// `row`: on return thread t holds the values at block positions 16 t + r in
-// x[r].  Uses all of `lds`; the caller needs a barrier before touching it
-// again unless it only writes the words it is handed (positions 16 t + r).
 // Thread t's values t + 256 r of block B: uint64 residues (SINGLE) or the
 // outer pass's fp64 intermediate.
 template <bool SINGLE>
@@ -613,8 +610,8 @@ struct LoadFrom {
 
 // Source of the inverse inner pass: row blockIdx.z of source blockIdx.y of a
 // key-switch table (out of place; the row receives the result).  A product
-// source (src_y set) is formed here, x y mod q in (-q/2, q/2] (balanced
-// values sit inside the inverse butterflies' input bound).
+// source (src_y set) is formed here, x y mod q within 0.875 q (mul_bound of two
+// canonical operands), inside the bound q from which the inverse stages start.
 struct LoadSources {
   KsTable tab;
   __device__ __forceinline__ void operator()(const uint64_t*, uint32_t off, double (&x)[16],
@@ -1052,8 +1049,11 @@ hipError_t launch_ntt_fwd_ks_combine(const Context* c, uint64_t* y, uint32_t njo
 }
 
 // (Splitting a large batch into cache-sized chunks, so that the second pass
-// would read the first pass's output back from the 256 MB Infinity Cache,
-// measured no faster on MI355X than one launch per pass over the whole batch.)
+// would read the first pass's output back from the 256 MB Infinity Cache, a launch
+// per pass and chunk, measured no faster than one launch per pass over the whole
+// batch.  With a chunk's second pass and the next one's first in one launch 64 x 24
+// limbs gained 3%, 1463 -> 1413 us with the MAC, and 25 x 24 lost 6%, 550 -> 584; not
+// taken.)
 hipError_t launch_ntt_rows(const Context* c, const RowSel& rs, uint32_t batch, uint32_t limbs,
                            bool inverse, hipStream_t s) {
   if (inverse) return launch_inverse(c, rs, batch, limbs, LoadRow{}, InvCanon{}, s);
