@@ -57,12 +57,15 @@ def rule(ask):
 # (log N, primes of the longest digit, target rows, digits) of one conversion launch
 FUSED = [(13, 1, 4, 4), (14, 1, 12, 12), (16, 1, 4, 2), (14, 2, 16, 8), (16, 2, 8, 4),
          (13, 3, 24, 32), (14, 3, 24, 2), (15, 3, 12, 8), (16, 3, 6, 4), (13, 5, 12, 2),
-         (13, 9, 9, 2), (14, 9, 9, 2)]
+         (13, 9, 9, 2), (14, 9, 9, 2), (15, 3, 3, 48), (15, 3, 9, 20), (16, 3, 9, 6), (16, 2, 6, 16),
+         (14, 9, 4, 32), (15, 9, 3, 40), (16, 10, 2, 16)]
 SEPARATE_ONE = [(15, 9, 9, 2), (15, 9, 24, 3), (13, 12, 24, 4), (15, 12, 24, 2), (13, 16, 24, 2),
-                (14, 16, 24, 4), (16, 9, 9, 4), (12, 1, 4, 4), (12, 16, 24, 16)]
+                (14, 16, 24, 4), (16, 9, 9, 4), (12, 1, 4, 4), (12, 16, 24, 16), (15, 9, 9, 4),
+                (16, 12, 3, 6), (16, 16, 3, 6)]
 SEPARATE_THREE = [(16, 9, 24, 3), (16, 12, 24, 2), (14, 12, 24, 8), (13, 16, 24, 16), (15, 9, 18, 8),
                   (15, 3, 24, 16), (16, 3, 12, 8), (13, 3, 24, 64), (16, 1, 12, 48),
-                  (12, 1, 24, 192), (13, 50, 50, 4096)]
+                  (12, 1, 24, 192), (13, 50, 50, 4096), (14, 3, 24, 20), (15, 3, 12, 20),
+                  (16, 3, 12, 8), (15, 9, 6, 24)]
 
 
 def test_forms(rule):

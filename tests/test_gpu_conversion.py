@@ -34,15 +34,16 @@ def _key(P, seed):
 # alpha 3 | 4: the two sides of the choice of unit; 8: nine sources in the
 # merged product; 9: past the matrix-core tables; levels with a last digit of
 # one prime or a single one shorter than alpha, and target counts of every
-# remainder mod 4; digits past the tables in each of the VALU's
-# forms (13, 9: fused, 16, 12: one target per workgroup, 14, 12: three).  alpha 8
-# at every ring on both sides of 8 M digits = 768, past which the matrix cores
+# remainder mod 4; digits past the tables in each of the VALU's forms (13, 9 and, a
+# batch with few rows, 14, 9: fused, 16, 12: one target per workgroup, 14, 12: three).
+# alpha 8 at every ring on both sides of 8 M digits = 768, past which the matrix cores
 # read digits that a pass of their own has finished (no such pass at N = 4096)
 @pytest.mark.parametrize("log_n,bits,L,alpha,level,count", [
     (12, 50, 7, 3, 7, 1), (12, 50, 9, 4, 9, 1), (12, 36, 10, 4, 10, 33),
     (13, 50, 9, 8, 9, 1), (13, 36, 6, 5, 6, 5), (14, 50, 9, 8, 9, 2), (14, 45, 10, 9, 10, 1),
     (15, 50, 7, 6, 7, 1), (15, 50, 4, 3, 4, 24), (16, 50, 5, 4, 5, 1), (16, 36, 3, 2, 3, 1),
     (16, 50, 5, 12, 5, 1), (13, 45, 9, 9, 9, 1), (14, 36, 12, 12, 12, 8),
+    (15, 50, 3, 3, 3, 24), (14, 50, 4, 9, 4, 16),
     (12, 50, 9, 8, 9, 2), (13, 50, 9, 8, 9, 32), (14, 50, 9, 8, 9, 16), (15, 50, 9, 8, 9, 1),
     (15, 50, 9, 8, 9, 8), (16, 50, 9, 8, 9, 1), (16, 50, 9, 8, 9, 4),
 ])
